@@ -96,7 +96,7 @@ __device__ __forceinline__ bool in_wall_zone(const Replica& R, int x) {
     return zone;
 }
 
-enum GatherKind { G_INTERIOR = 0, G_FAST = 1, G_WALL_PLANE = 2, G_WALL = 3, G_GENERIC = 4 };
+enum GatherKind { G_INTERIOR = 0, G_FAST = 1, G_WALL_PLANE = 2, G_WALL = 3, G_FACE = 4, G_GENERIC = 5 };
 
 // Element `node` of a population block that starts at the wave-uniform pointer bp.  The byte
 // offset is formed in 32 bits (a replica's population block holds at most 4 GiB, which
@@ -109,7 +109,8 @@ __device__ __forceinline__ T ld32(const T* __restrict__ bp, int node) {
 
 // Incoming populations of one lane of the flattened mapping (64 consecutive nodes
 // per wave, possibly spanning rows), as stored numbers (Codec::load_raw).
-//  G_GENERIC:    any lane (full resolver, used by waves touching a y/z face);
+//  G_GENERIC:    any lane (full resolver, used by waves touching a y/z face and a wall);
+//  G_FACE:       lanes on any face, no wall within one node;
 //  G_WALL:       y and z interior, lanes may neighbour a wall and its pore (solid test per
 //                source over the 27 neighbours);
 //  G_WALL_PLANE: y and z interior, lanes may neighbour a wall but lie at least two nodes from
@@ -117,7 +118,7 @@ __device__ __forceinline__ T ld32(const T* __restrict__ bp, int node) {
 //                wall plane: only populations with c_x != 0 can bounce, on two per-lane bits;
 //  G_FAST:       y and z interior, no wall within one node (only x faces need care);
 //  G_INTERIOR:   no lane on any face or within one node of a wall (no test at all).
-// Outside G_GENERIC each population is read from its own block at a 32-bit offset; a
+// Outside G_GENERIC and G_FACE each population is read from its own block at a 32-bit offset; a
 // free-slip x face (the reflected population at the node itself) and a solid source (the
 // node's own population opp(p), half-way bounce-back) are loads of their own, taken only
 // by the lanes that need them.
@@ -136,14 +137,14 @@ __device__ __forceinline__ void gather19(
     const long long PS = R.S;  // population plane stride
     const int nx = R.nx, nxy = R.nx * R.ny;
     const T* __restrict__ base = src + R.pop_base;
-    if constexpr (KIND == G_GENERIC) {
+    if constexpr (KIND == G_GENERIC || KIND == G_FACE) {
+        constexpr bool walls = KIND == G_GENERIC;
+        const PullMap map = make_pull_map<walls>(R, x, y, z);
         for_pops([&](auto P) {
             constexpr int p = decltype(P)::value;
-            int q;
-            const int node = pull_source<p>(R, x, y, z, &q);
-            // q differs from p only by reflections or reversal, which keep the weight
-            // class, so the codec scale of p applies to slot q
-            f[p] = cv(base[(long long)q * PS + node]);
+            // the source population differs from p only by reflections or reversal, which
+            // keep the weight class, so the codec scale of p applies to it
+            f[p] = cv(base[pull_element<p, walls>(R, map)]);
         });
         return;
     }
@@ -560,7 +561,8 @@ __global__ __launch_bounds__(BLOCK) void k_stream_collide(const Replica* __restr
         if (!inside) return;
         solid = !active;
         if (active) {
-            if (any_face) gather19<S, G_GENERIC>(R, src, idx, x, y, z, f);
+            if (any_face && any_zone) gather19<S, G_GENERIC>(R, src, idx, x, y, z, f);
+            else if (any_face) gather19<S, G_FACE>(R, src, idx, x, y, z, f);
             else if (any_pore) gather19<S, G_WALL>(R, src, idx, x, y, z, f);
             else if (any_zone) gather19<S, G_WALL_PLANE>(R, src, idx, x, y, z, f);
             else if (any_xface) gather19<S, G_FAST>(R, src, idx, x, y, z, f);
@@ -647,7 +649,8 @@ __global__ __launch_bounds__(BLOCK) void k_stream_collide_2n(const Replica* __re
     // 16-bit elements are gathered as stored and decoded after both nodes' loads are issued
     using E = std::conditional_t<C::deviation, typename C::T, Rl>;
     E g0[Q], g1[Q];
-    if (any_face) gather_two<S, G_GENERIC>(R, src, n, x, y, z, g0, g1);
+    if (any_face && any_zone) gather_two<S, G_GENERIC>(R, src, n, x, y, z, g0, g1);
+    else if (any_face) gather_two<S, G_FACE>(R, src, n, x, y, z, g0, g1);
     else if (any_pore) gather_two<S, G_WALL>(R, src, n, x, y, z, g0, g1);
     else if (any_zone) gather_two<S, G_WALL_PLANE>(R, src, n, x, y, z, g0, g1);
     else if (any_xface) gather_two<S, G_FAST>(R, src, n, x, y, z, g0, g1);
@@ -782,12 +785,15 @@ template <int S>
 __device__ __forceinline__ void gather_f64(const Replica& R, const typename Codec<S>::T* __restrict__ src,
                                            int x, int y, int z, double* f) {
     using C = Codec<S>;
-    const long long PS = R.S;  // population plane stride
+    const PullMap map = make_pull_map(R, x, y, z);
+    typename C::T raw[Q];
     for_pops([&](auto P) {
         constexpr int p = decltype(P)::value;
-        int q;
-        const int node = pull_source<p>(R, x, y, z, &q);
-        double v = (double)C::template load<p>(src[R.pop_base + (long long)q * PS + node]);
+        raw[p] = src[R.pop_base + pull_element<p>(R, map)];
+    });
+    for_pops([&](auto P) {
+        constexpr int p = decltype(P)::value;
+        double v = (double)C::template load<p>(raw[p]);
         if constexpr (C::deviation) v += w_of<double>(p) * R.rho0;
         f[p] = v;
     });
@@ -862,7 +868,8 @@ __global__ __launch_bounds__(256) void k_conserved_partial(const Replica R,
         const bool any_xface = __ballot(fluid && (x == 0 || x == R.nx - 1)) != 0;
         if (!fluid) continue;
         Rl f[Q];
-        if (any_face) gather19<S, G_GENERIC>(R, src, idx, x, y, z, f);
+        if (any_face && any_zone) gather19<S, G_GENERIC>(R, src, idx, x, y, z, f);
+        else if (any_face) gather19<S, G_FACE>(R, src, idx, x, y, z, f);
         else if (any_pore) gather19<S, G_WALL>(R, src, idx, x, y, z, f);
         else if (any_zone) gather19<S, G_WALL_PLANE>(R, src, idx, x, y, z, f);
         else if (any_xface) gather19<S, G_FAST>(R, src, idx, x, y, z, f);

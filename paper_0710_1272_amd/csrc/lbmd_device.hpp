@@ -275,6 +275,71 @@ __host__ __device__ __forceinline__ int pull_source(const Replica& R, int x, int
     return s;
 }
 
+// The pull sources of all 19 populations of one fluid node, resolved without a branch per
+// population.  pull_source's tests compile to control flow around every population, which puts
+// a wait between one population's load and the next: a gather through it is 19 dependent round
+// trips (12 us of the bead kernel's 37 us at 128x64x64).  Here each axis resolves its two
+// neighbour coordinates once (wrapped, or kept and reflected), each wall folds into the
+// solidity bits of the 27 resolved neighbours, and a population's element is selects over
+// those, so that the caller can issue all 19 loads before it uses the first.
+struct PullMap {
+    int c[3][3];       // resolved coordinate at -1, 0, +1 of the node, per axis
+    bool refl[3][2];   // whether the neighbour at -1, +1 lies behind a free-slip face, per axis
+    unsigned solid27;  // solidity of the resolved neighbours, bit 9 (dx+1) + 3 (dy+1) + (dz+1)
+    int node;          // the node itself
+};
+
+// WALLS = false: the node has no wall within one plane in x, so that no source is solid
+template <bool WALLS = true>
+__host__ __device__ __forceinline__ PullMap make_pull_map(const Replica& R, int x, int y, int z) {
+    PullMap m;
+    const int n[3] = {R.nx, R.ny, R.nz}, g[3] = {x, y, z};
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const bool lo = g[a] == 0, hi = g[a] == n[a] - 1, fs = R.fs[a] != 0;
+        m.c[a][0] = lo ? (fs ? g[a] : n[a] - 1) : g[a] - 1;
+        m.c[a][1] = g[a];
+        m.c[a][2] = hi ? (fs ? g[a] : 0) : g[a] + 1;
+        m.refl[a][0] = lo && fs;
+        m.refl[a][1] = hi && fs;
+    }
+    m.node = x + R.nx * (y + R.ny * z);
+    m.solid27 = 0u;
+    if constexpr (!WALLS) return m;
+#pragma unroll
+    for (int k = 0; k < LB_MAX_WALLS; ++k) {
+        if (k >= R.n_walls) break;
+        const int* w = R.wall[k];
+        const bool open = pore_open(w);
+        unsigned b[3] = {0u, 0u, 0u};
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int d = 0; d < 3; ++d)
+                b[a] |= (unsigned)(m.c[a][d] >= w[2 * a] && m.c[a][d] <= w[2 * a + 1]) << d;
+        // pore membership of the nine (dy, dz), bit 3 (dy+1) + (dz+1)
+        const unsigned yz = ((b[1] & 1u) ? b[2] : 0u) | ((b[1] & 2u) ? b[2] << 3 : 0u) | ((b[1] & 4u) ? b[2] << 6 : 0u);
+        const unsigned closed = open ? ~yz & 0x1FFu : 0x1FFu;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) m.solid27 |= (b[0] >> d) & 1u ? closed << (9 * d) : 0u;
+    }
+    return m;
+}
+
+// element offset, from the replica's population block, of the value that arrives in (node, P)
+template <int P, bool WALLS = true>
+__host__ __device__ __forceinline__ long long pull_element(const Replica& R, const PullMap& m) {
+    constexpr int cx = cx_of(P), cy = cy_of(P), cz = cz_of(P);
+    constexpr int bit = 9 * (1 - cx) + 3 * (1 - cy) + (1 - cz);
+    int q = mirror_combo<P>(cx != 0 && m.refl[0][cx > 0 ? 0 : 1], cy != 0 && m.refl[1][cy > 0 ? 0 : 1],
+                            cz != 0 && m.refl[2][cz > 0 ? 0 : 1]);
+    const int s = m.c[0][1 - cx] + R.nx * (m.c[1][1 - cy] + R.ny * m.c[2][1 - cz]);
+    if constexpr (!WALLS) return (long long)q * R.S + s;
+    const bool solid = (m.solid27 >> bit) & 1u;
+    q = solid ? opp_of(P) : q;
+    return (long long)q * R.S + (solid ? m.node : s);
+}
+
 // Face resolution of the push target of population QP leaving node (sx,sy,sz), the inverse of
 // pull_resolve: t = s + c_QP, a periodic axis wraps, a free-slip axis keeps s_a and reflects
 // component a.  No solidity test.  Returns the node index, its coordinates in tc[3] and the
