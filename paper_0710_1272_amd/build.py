@@ -12,6 +12,8 @@ CSRC = os.path.join(PKG, "csrc")
 LIBDIR = os.path.join(PKG, "_lib")
 LIB = os.path.join(LIBDIR, "liblbmd.so")
 SOURCES = ["lb_kernels.hip", "md_kernels.hip", "lbmd_api.hip"]
+# the bead kernel's variants, each an object of its own: (arithmetic type, periodic axes, polymer model)
+BEAD_VARIANTS = [(real, per, poly) for real in ("double", "float") for poly in (1, 0) for per in (1, 0)]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -25,11 +27,16 @@ FLAGS = [
 
 def build(verbose: bool = False) -> str:
     os.makedirs(LIBDIR, exist_ok=True)
-    objs = [os.path.join(LIBDIR, s.replace(".hip", ".o")) for s in SOURCES]
+    units = [(s, s.replace(".hip", ".o"), []) for s in SOURCES]
+    for real, per, poly in BEAD_VARIANTS:
+        units.append(("md_bead.hip", f"md_bead_{real}_{per}{poly}.o",
+                      [f"-DMD_REAL={real}", f"-DMD_PERIODIC={per}", f"-DMD_POLY={poly}"]))
+    units = [(src, os.path.join(LIBDIR, obj), defs) for src, obj, defs in units]
+    objs = [obj for _, obj, _ in units]
 
-    def compile_one(src_obj):
-        src, obj = src_obj
-        cmd = [HIPCC, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+    def compile_one(unit):
+        src, obj, defs = unit
+        cmd = [HIPCC, *FLAGS, *defs, "-c", os.path.join(CSRC, src), "-o", obj]
         r = subprocess.run(cmd, capture_output=True, text=True)
         out = "\n".join(l for l in (r.stdout + r.stderr).splitlines() if "packed-fp32-ops" not in l)
         if r.returncode != 0:
@@ -37,8 +44,8 @@ def build(verbose: bool = False) -> str:
         if verbose and out.strip():
             print(out, file=sys.stderr)
 
-    with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
-        list(ex.map(compile_one, zip(SOURCES, objs)))
+    with ThreadPoolExecutor(max_workers=min(len(units), 8)) as ex:
+        list(ex.map(compile_one, units))
     tmp = LIB + ".tmp"
     r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp],
                        capture_output=True, text=True)
