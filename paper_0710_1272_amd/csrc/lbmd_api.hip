@@ -922,7 +922,8 @@ int lb_init(const lbmd_config* cfg, const lbmd_buffers* bufs, void* hip_stream, 
     if ((rc = check(hipStreamCreateWithFlags(&c.cap, hipStreamNonBlocking), "capture stream"))) return bail(rc);
     if ((rc = check(hipEventCreateWithFlags(&c.ev_fork, hipEventDisableTiming), "event"))) return bail(rc);
     if ((rc = check(hipEventCreateWithFlags(&c.ev_join, hipEventDisableTiming), "event"))) return bail(rc);
-    if ((rc = check(hipHostMalloc((void**)&c.h_small, 32 * sizeof(double), hipHostMallocDefault),
+    if ((rc = check(hipHostMalloc((void**)&c.h_small, (4 + std::max<size_t>(8, 7 * (size_t)c.max_beads)) * sizeof(double),
+                                  hipHostMallocDefault),
                     "pinned staging")))
         return bail(rc);
 
@@ -1083,42 +1084,6 @@ int lb_md_lanes(const lbmd_ctx* ctx) {
 
 }  // extern "C"
 
-namespace {
-
-template <class Real>
-int copy_bead_field(Context& c, const Replica& R, const Real* dev, int ncomp, double* out) {
-    const int n = R.n_beads, N = c.ntot_beads;
-    std::vector<Real> tmp((size_t)n);
-    for (int a = 0; a < ncomp; ++a) {
-        HIP_TRY(hipMemcpyAsync(tmp.data(), dev + (size_t)a * N + R.bead0, n * sizeof(Real), hipMemcpyDeviceToHost, c.stream));
-        HIP_TRY(hipStreamSynchronize(c.stream));
-        for (int i = 0; i < n; ++i) out[(size_t)ncomp * i + a] = (double)tmp[i];
-    }
-    return LB_OK;
-}
-
-template <class Real>
-int moments_beads(Context& c, int replica, unsigned what, double* out) {
-    const BeadPtrs<Real>& b = *(const BeadPtrs<Real>*)c.bead_ptrs;
-    const Replica& R = c.reps[replica];
-    const int n = R.n_beads;
-    if (n == 0) return LB_OK;
-    int rc;
-    if (what == LB_MOM_BEADS) {
-        if ((rc = copy_bead_field<double>(c, R, b.r, 3, out))) return rc;
-        return copy_bead_field<Real>(c, R, b.v, 3, out + 3 * (size_t)n);
-    }
-    if ((rc = copy_bead_field<Real>(c, R, b.u, 3, out))) return rc;
-    if ((rc = copy_bead_field<Real>(c, R, b.fbar, 3, out + 3 * (size_t)n))) return rc;
-    std::vector<int> nd((size_t)n);
-    HIP_TRY(hipMemcpyAsync(nd.data(), b.node + R.bead0, n * sizeof(int), hipMemcpyDeviceToHost, c.stream));
-    HIP_TRY(hipStreamSynchronize(c.stream));
-    for (int i = 0; i < n; ++i) out[6 * (size_t)n + i] = nd[i];
-    return LB_OK;
-}
-
-}  // namespace
-
 extern "C" {
 
 int lb_moments(lbmd_ctx* ctx, int replica, unsigned what, void* host_out, size_t bytes) {
@@ -1132,16 +1097,14 @@ int lb_moments(lbmd_ctx* ctx, int replica, unsigned what, void* host_out, size_t
     const Replica& R = c.reps[replica];
     const void* cur = c.pops[c.cur];
     // every read below is ordered on the context's stream after the queued steps; small
-    // results travel through pinned staging with the run state, one synchronisation
-    double* hs = c.h_small;
-    RunState* hst = (RunState*)(hs + 16);
+    // results and the run state are written to pinned staging, one synchronisation
+    RunState* hst = (RunState*)c.h_small;
+    double* hs = c.h_small + 4;
+    int small = READ_STATE;
     switch (what) {
-        case LB_MOM_CONSERVED: {
-            double* d_out4 = c.d_partials + 4 * (size_t)c.partial_blocks;
-            HIP_TRY(launch_conserved(c, replica, cur, d_out4, c.stream));
-            HIP_TRY(hipMemcpyAsync(hs, d_out4, 4 * sizeof(double), hipMemcpyDeviceToHost, c.stream));
+        case LB_MOM_CONSERVED:
+            HIP_TRY(launch_conserved(c, replica, cur, hs, c.stream));
             break;
-        }
         case LB_MOM_FIELDS:
         case LB_MOM_POPULATIONS: {
             const int ncomp = what == LB_MOM_FIELDS ? 4 : 19;
@@ -1155,21 +1118,9 @@ int lb_moments(lbmd_ctx* ctx, int replica, unsigned what, void* host_out, size_t
             }
             break;
         }
-        case LB_MOM_BEADS:
-        case LB_MOM_COUPLING: {
-            int rc = c.storage == LB_STORE_F64 ? moments_beads<double>(c, replica, what, out)
-                                               : moments_beads<float>(c, replica, what, out);
-            if (rc) return rc;
-            break;
-        }
-        case LB_MOM_TRANSLOC: {
-            const double* diag = c.storage == LB_STORE_F64 ? ((BeadPtrs<double>*)c.bead_ptrs)->diag
-                                                           : ((BeadPtrs<float>*)c.bead_ptrs)->diag;
-            HIP_TRY(hipMemcpyAsync(hs, diag + 8 * replica, 8 * sizeof(double), hipMemcpyDeviceToHost, c.stream));
-            break;
-        }
-        case LB_MOM_STATUS:
-            break;
+        case LB_MOM_BEADS: small = READ_BEADS; break;
+        case LB_MOM_COUPLING: small = READ_COUPLING; break;
+        case LB_MOM_TRANSLOC: small = READ_TRANSLOC; break;
         case LB_MOM_OBSERVABLES: {
             const double* obs = c.storage == LB_STORE_F64 ? ((BeadPtrs<double>*)c.bead_ptrs)->obs
                                                           : ((BeadPtrs<float>*)c.bead_ptrs)->obs;
@@ -1178,12 +1129,15 @@ int lb_moments(lbmd_ctx* ctx, int replica, unsigned what, void* host_out, size_t
                                    hipMemcpyDeviceToHost, c.stream));
             break;
         }
+        default: break;
     }
-    HIP_TRY(hipMemcpyAsync(hst, c.d_state, sizeof(RunState), hipMemcpyDeviceToHost, c.stream));
+    HIP_TRY(launch_readout(c, small, replica, hs, hst, c.stream));
     HIP_TRY(hipStreamSynchronize(c.stream));
     const RunState st = *hst;
     if (what == LB_MOM_CONSERVED) {
         for (int k = 0; k < 4; ++k) out[k] = hs[k];
+    } else if (what == LB_MOM_BEADS || what == LB_MOM_COUPLING) {
+        std::memcpy(out, hs, need);
     } else if (what == LB_MOM_TRANSLOC) {
         for (int k = 0; k < 5; ++k) out[k] = hs[k];
         out[5] = (double)c.host_step;

@@ -66,7 +66,8 @@ struct Context {
     void* beads = nullptr;
     void* work = nullptr;
     bool owns_buffers = false;
-    double* h_small = nullptr;         // pinned host staging for small read-outs (32 doubles)
+    double* h_small = nullptr;         // pinned host staging for small read-outs: run state (4
+                                       // doubles), then 8 doubles or 7 per bead of one replica
     int cur = 0;                       // which pops buffer holds the current state
     long long host_step = 0;           // mirror of the device step counter
 
@@ -134,6 +135,10 @@ std::string replica_problem(const lbmd_replica& R);
 hipError_t launch_md(const Context& c, const void* cur, int mode, hipStream_t s);
 hipError_t launch_spread(const Context& c, void* dst, bool bump_step, hipStream_t s);
 hipError_t launch_bump(const Context& c, hipStream_t s);
+// one replica's bead state, coupling data or diagnostics, and the run state, written to pinned
+// host memory (readable after a synchronisation of s)
+enum ReadOut : int { READ_STATE = 0, READ_BEADS = 1, READ_COUPLING = 2, READ_TRANSLOC = 3 };
+hipError_t launch_readout(const Context& c, int what, int replica, double* out, RunState* out_st, hipStream_t s);
 // step 1 with the trilinear stencil (a kernel of its own; the bead kernel then runs its
 // substeps on the interpolated velocities)
 hipError_t launch_interp_trilinear(const Context& c, const void* cur, hipStream_t s);

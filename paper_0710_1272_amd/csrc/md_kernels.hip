@@ -59,6 +59,34 @@ __global__ __launch_bounds__(256) void k_spread(const Replica* __restrict__ reps
 
 __global__ void k_bump(RunState* st) { st->step += 1; }
 
+// Small read-outs straight into pinned host memory, the run state with them: one launch and one
+// synchronisation a call.  Copy commands instead (one per component of each bead array, each
+// with a synchronisation of its own) took 130 us for the bead state of 100 beads, 10 us of it
+// the copies themselves; this takes 16 us.
+//   beads:    out = [n][3] positions, [n][3] velocities
+//   coupling: out = [n][3] u_i, [n][3] Fbar_i, [n] node index
+//   transloc: out = the replica's 8 diagnostics
+template <class Real>
+__global__ __launch_bounds__(256) void k_readout(BeadPtrs<Real> b, const RunState* __restrict__ st, int what,
+                                                 int replica, int b0, int n, double* __restrict__ out,
+                                                 RunState* __restrict__ out_st) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i == 0) *out_st = *st;
+    const int NT = b.ntot;
+    if (what == READ_TRANSLOC) {
+        if (i < 8) out[i] = b.diag[8 * replica + i];
+        return;
+    }
+    if (i >= n || what == READ_STATE) return;
+    const int g = b0 + i;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        out[3 * i + c] = what == READ_BEADS ? b.r[c * NT + g] : (double)b.u[c * NT + g];
+        out[3 * (n + i) + c] = what == READ_BEADS ? (double)b.v[c * NT + g] : (double)b.fbar[c * NT + g];
+    }
+    if (what == READ_COUPLING) out[6 * n + i] = (double)b.node[g];
+}
+
 // Observable record of the translocation analysis (Sec. III), one workgroup per replica,
 // after the bead step and before the step counter moves: when (step + 1) is a multiple of
 // obs_every, a row (step + 1, N_T, S_H = m gamma sum v.u, S_E = sum F_drive.v over beads on
@@ -514,6 +542,21 @@ hipError_t launch_observe(const Context& c, bool no_hydro, hipStream_t s) {
     if (c.obs_every <= 0 || c.ntot_beads == 0) return hipSuccess;
     return c.storage == LB_STORE_F64 ? launch_observe_t<double>(c, no_hydro, s)
                                      : launch_observe_t<float>(c, no_hydro, s);
+}
+
+template <class Real>
+static hipError_t launch_readout_t(const Context& c, int what, int r, double* out, RunState* out_st, hipStream_t s) {
+    const BeadPtrs<Real> b = *(const BeadPtrs<Real>*)c.bead_ptrs;
+    const Replica& R = c.reps[r];
+    const int grid = what == READ_BEADS || what == READ_COUPLING ? (R.n_beads + 255) / 256 : 1;
+    hipLaunchKernelGGL((k_readout<Real>), dim3(grid > 0 ? grid : 1), dim3(256), 0, s, b, c.d_state, what, r, R.bead0,
+                       R.n_beads, out, out_st);
+    return hipGetLastError();
+}
+
+hipError_t launch_readout(const Context& c, int what, int r, double* out, RunState* out_st, hipStream_t s) {
+    return c.storage == LB_STORE_F64 ? launch_readout_t<double>(c, what, r, out, out_st, s)
+                                     : launch_readout_t<float>(c, what, r, out, out_st, s);
 }
 
 hipError_t launch_bump(const Context& c, hipStream_t s) {

@@ -300,7 +300,7 @@ class Simulation:
         nbytes = L.lb_moments_bytes(self.ctx, replica, what)
         if nbytes == 0:
             raise ValueError("invalid replica or observable")
-        out = np.zeros(nbytes // 8, dtype=np.float64)
+        out = np.empty(nbytes // 8, dtype=np.float64)  # lb_moments writes all of it
         rc = L.lb_moments(self.ctx, replica, what, out.ctypes.data_as(C.c_void_p), nbytes)
         if rc == LB_EUNSTABLE and allow_unstable:
             return out
