@@ -373,57 +373,56 @@ __device__ __forceinline__ void angle_forces(const double* ra, const double* rb,
     }
 }
 
+// 1/b in FP64 to about an ulp: the hardware estimate and two Newton steps (an IEEE division is
+// twice as many dependent instructions)
+__device__ __forceinline__ double rcp64(double b) {
+    double r = __builtin_amdgcn_rcp(b);
+    r = __builtin_fma(__builtin_fma(-b, r, 1.0), r, r);
+    return __builtin_fma(__builtin_fma(-b, r, 1.0), r, r);
+}
+
+// Whether any thread of the block passes need = true.  Two words, used in turn by successive
+// votes (stamp counts them), so that nothing has to be cleared; between two votes on one word
+// lies the barrier of the vote in between.
+__device__ __forceinline__ bool block_vote(int* words, int stamp, bool need) {
+    if (__ballot(need) != 0ull && (threadIdx.x & 63) == 0) words[stamp & 1] = ~stamp;
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(words[stamp & 1]) == ~stamp;
+}
+
 // One tridiagonal system a_t x_{t-1} + b_t x_t + c_t x_{t+1} = d_t per workgroup, row t
 // held by thread t (t < m), solved by parallel cyclic reduction: at stride s each row
-// eliminates its couplings to rows t - s and t + s (rows outside 0..m-1 are identities),
-// so after ceil(log2 m) levels x_t = d_t / b_t.  Each row publishes 1/b with a, c, d, so a
-// level takes one division (the row's own new 1/b) instead of two.  Double-buffered in LDS
-// (W: [2][4][nmax] doubles: a, 1/b, c, d); one barrier per level.  Every thread of the
-// block must call it.
-// With `vote`, the barrier after the first writes also returns whether any thread passed
-// need = true in *any; without any, or with solve = false, no level runs and 0 is returned
-// (a Newton step folds its convergence test into the solve that follows it this way).
-__device__ __forceinline__ double pcr_solve(double* W, int nmax, int m, int t, double a, double b, double c,
-                                            double d, bool vote = false, bool need = true, bool solve = true,
-                                            bool* any = nullptr) {
+// eliminates its couplings to rows t - s and t + s, so after ceil(log2 m) levels x_t = d_t / b_t.
+// A level is a chain of one LDS round trip, a dozen dependent FP64 operations and a barrier, and
+// a rigid chain's step is mostly such chains: rows are published as (a, 1/b, c, d), two 16-byte
+// reads a neighbour; a row's coupling beyond either end is zero from the start and stays zero,
+// so that the neighbour index is only clamped; and the new 1/b is a refined estimate, not a
+// division.  The coupled step of 128x64x64 with a rigid chain of 100 beads (M = 5, FP32) fell from
+// 99.6 to 77.4 us with it (before: one 8-byte array per coefficient, an IEEE division and a bounds
+// test per neighbour and level).  W: [2][nmax][4] doubles, the two halves used in turn.  Every
+// thread of the block must call it; it ends behind a barrier.
+struct alignas(16) PcrRow {
+    double a, ib, c, d;
+};
+__device__ __forceinline__ double pcr_solve(PcrRow* W, int nmax, int m, int t, double a, double b, double c, double d) {
     const bool row = t < m;
-    int buf = 0;
-    double ib = 1.0 / b;
-    if (row) {
-        W[(0 * 4 + 0) * nmax + t] = a;
-        W[(0 * 4 + 1) * nmax + t] = ib;
-        W[(0 * 4 + 2) * nmax + t] = c;
-        W[(0 * 4 + 3) * nmax + t] = d;
-    }
-    if (vote) {
-        const bool any_need = __syncthreads_or(need) != 0;
-        *any = any_need;
-        if (!any_need || !solve) return 0.0;
-    } else {
-        __syncthreads();
-    }
+    double ib = rcp64(b);
+    if (row) W[t] = PcrRow{a, ib, c, d};
+    __syncthreads();
+    int from = 0;
     for (int s = 1; s < m; s <<= 1) {
-        const double* Ws = W + buf * 4 * nmax;
-        double* Wd = W + (buf ^ 1) * 4 * nmax;
         if (row) {
-            const int lo = t - s, hi = t + s;
-            const double al = lo >= 0 ? Ws[lo] : 0.0, ibl = lo >= 0 ? Ws[nmax + lo] : 1.0;
-            const double cl = lo >= 0 ? Ws[2 * nmax + lo] : 0.0, dl = lo >= 0 ? Ws[3 * nmax + lo] : 0.0;
-            const double ah = hi < m ? Ws[hi] : 0.0, ibh = hi < m ? Ws[nmax + hi] : 1.0;
-            const double ch = hi < m ? Ws[2 * nmax + hi] : 0.0, dh = hi < m ? Ws[3 * nmax + hi] : 0.0;
-            const double k1 = a * ibl, k2 = c * ibh;
-            const double na = -al * k1, nc = -ch * k2;
-            b = b - cl * k1 - ah * k2;
-            d = d - dl * k1 - dh * k2;
-            a = na;
-            c = nc;
-            ib = 1.0 / b;
-            Wd[t] = a;
-            Wd[nmax + t] = ib;
-            Wd[2 * nmax + t] = c;
-            Wd[3 * nmax + t] = d;
+            const PcrRow l = W[from + (t - s > 0 ? t - s : 0)];
+            const PcrRow h = W[from + (t + s < m ? t + s : m - 1)];
+            const double k1 = a * l.ib, k2 = c * h.ib;
+            b = b - l.c * k1 - h.a * k2;
+            d = d - l.d * k1 - h.d * k2;
+            a = -l.a * k1;
+            c = -h.c * k2;
+            ib = rcp64(b);
+            if (2 * s < m) W[nmax - from + t] = PcrRow{a, ib, c, d};
         }
-        buf ^= 1;
+        from = nmax - from;
         __syncthreads();
     }
     return row ? d * ib : 0.0;
@@ -532,7 +531,7 @@ __device__ __forceinline__ const Args& reread_args() {
 
 template <class Real, int G, int BPT, bool PERIODIC, int MAXT, bool POLY>
 __global__ __launch_bounds__(MAXT) void k_md(MDKArgs<Real> a, int storage) {
-    extern __shared__ double lds[];
+    extern __shared__ __align__(16) double lds[];
     __shared__ double red[16 * 4];
     const int NG = blockDim.x / G;  // groups per block
     const Replica& R = a.reps[blockIdx.x];
@@ -566,7 +565,7 @@ __global__ __launch_bounds__(MAXT) void k_md(MDKArgs<Real> a, int storage) {
     double* SDV = RW;
     double* LAM = RW + 3 * nmax;
     double* VXV = RW + 4 * nmax;
-    double* PCRW = RW + 7 * nmax;
+    PcrRow* PCRW = (PcrRow*)(RW + 7 * nmax);
     const int M = md.M;
     const long long step = a.st->step;
     const int* nn = GM.n;
@@ -750,8 +749,9 @@ __global__ __launch_bounds__(MAXT) void k_md(MDKArgs<Real> a, int storage) {
     // divergent in the compiler's eyes, and every decision of the loop a vector branch).
     // Two words, so that one barrier per substep separates the writes of a substep from its
     // reads and from the next writes to the same word; nothing has to be cleared.
-    __shared__ int vote[2];
-    if (tid < 2) vote[tid] = 0;
+    __shared__ int vote[2], shake_vote[2];
+    if (tid < 2) vote[tid] = shake_vote[tid] = 0;
+    int votes = 0;  // rigid bonds: convergence votes taken
     __syncthreads();
 
     // chain neighbours (constant over the step) and the register slots of the lists
@@ -1112,18 +1112,16 @@ __global__ __launch_bounds__(MAXT) void k_md(MDKArgs<Real> a, int storage) {
                     g = (double)separation_v<double, PERIODIC>(ra, rb, per, nd, sv) - md.b2;
                 }
                 const bool bad = on && !(fabs(g) <= md.shake_tol_b2);
-                // the Jacobian is assembled before the vote, which the solve's first barrier takes
                 const double B = on ? 4.0 * im * (sv[0] * dref[0] + sv[1] * dref[1] + sv[2] * dref[2]) : 1.0;
                 const double Aa = on ? -2.0 * im * (sv[0] * dm1[0] + sv[1] * dm1[1] + sv[2] * dm1[2]) : 0.0;
                 const double Cc = on ? -2.0 * im * (sv[0] * dp1[0] + sv[1] * dp1[1] + sv[2] * dp1[2]) : 0.0;
-                bool any_bad = false;
-                const double x = pcr_solve(PCRW, nmax, m, t, Aa, B, Cc, on ? -g : 0.0, true, bad,
-                                           it < md.shake_iter, &any_bad);
+                const bool any_bad = block_vote(shake_vote, votes++, bad);
                 if (!any_bad) break;
                 if (it >= md.shake_iter) {
                     flags |= LB_ERR_CONSTRAINT;
                     break;
                 }
+                const double x = pcr_solve(PCRW, nmax, m, t, Aa, B, Cc, on ? -g : 0.0);
                 if (on) LAM[t] += x;
                 __syncthreads();
             }
