@@ -14,6 +14,8 @@ LIB = os.path.join(LIBDIR, "liblbmd.so")
 SOURCES = ["lb_kernels.hip", "md_kernels.hip", "lbmd_api.hip"]
 # the bead kernel's variants, each an object of its own: (arithmetic type, periodic axes, polymer model)
 BEAD_VARIANTS = [(real, per, poly) for real in ("double", "float") for poly in (1, 0) for per in (1, 0)]
+# the one-launch coupled step's variants: (storage, polymer model)
+STEP_VARIANTS = [(storage, poly) for poly in (1, 0) for storage in (0, 1, 2, 3)]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -31,6 +33,8 @@ def build(verbose: bool = False) -> str:
     for real, per, poly in BEAD_VARIANTS:
         units.append(("md_bead.hip", f"md_bead_{real}_{per}{poly}.o",
                       [f"-DMD_REAL={real}", f"-DMD_PERIODIC={per}", f"-DMD_POLY={poly}"]))
+    for storage, poly in STEP_VARIANTS:
+        units.append(("md_step.hip", f"md_step_{storage}_{poly}.o", [f"-DMD_STORAGE={storage}", f"-DMD_POLY={poly}"]))
     units = [(src, os.path.join(LIBDIR, obj), defs) for src, obj, defs in units]
     objs = [obj for _, obj, _ in units]
 

@@ -6,7 +6,9 @@
 //   join:  main stream  -> k_spread (S_p into the other buffer), step counter += 1
 // The lattice update does not need the beads (S_p is added after collision), so
 // the latency-bound MD of one workgroup per replica runs under the bandwidth-bound
-// lattice sweep.  The steps are captured once per buffer parity into HIP graphs.
+// lattice sweep.  One small box with nearest-node coupling takes the whole step in one launch
+// (k_step_one: the bead block updates the nodes its beads sit on, the other blocks the rest).
+// The steps are captured once per buffer parity into HIP graphs.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -149,7 +151,18 @@ Replica make_replica(const lbmd_replica& in, size_t elem) {
     return R;
 }
 
-WorkLayout work_layout(int n_reps, int max_V, long long max_stage_nodes) {
+// one box with beads, nearest-node coupling, free-slip faces and no thermal source
+int mark_chunks(const lbmd_config* cfg) {
+    if (cfg->n_replicas != 1 || cfg->md.stencil != LB_STENCIL_NGP) return 0;
+    const lbmd_replica& R = cfg->replicas[0];
+    const long long V = (long long)R.nx * R.ny * R.nz;
+    if (V > kStepOneNodes || R.n_chains < 1 || R.fluid_kT > 0.0) return 0;
+    for (int a = 0; a < 3; ++a)
+        if (R.bc[a] != LB_BC_FREESLIP) return 0;
+    return (int)((V + 63) / 64);
+}
+
+WorkLayout work_layout(int n_reps, int max_V, long long max_stage_nodes, int chunks) {
     WorkLayout L{};
     size_t off = 0;
     L.reps = off;
@@ -166,6 +179,12 @@ WorkLayout work_layout(int n_reps, int max_V, long long max_stage_nodes) {
     L.n_prefix_tables = 3 * kNumBlockSizes;
     L.prefix = off;
     off += align256(sizeof(int) * (size_t)(n_reps + 1) * kNumBlockSizes * 3);
+    // marks of two steps: stamps, then masks
+    L.chunks = chunks;
+    L.stamps = off;
+    off += align256(2 * sizeof(long long) * (size_t)chunks);
+    L.masks = off;
+    off += align256(2 * sizeof(unsigned long long) * (size_t)chunks);
     L.total = off;
     return L;
 }
@@ -307,7 +326,8 @@ size_t lb_required_bytes(const lbmd_config* cfg, int which) {
             return bead_layout(t.beads, cfg->n_replicas, real_size(cfg->storage), obs_rows(cfg),
                                t.beads > 0 && cfg->md.stencil == LB_STENCIL_TRILINEAR)
                 .total;
-        case LB_BUF_WORK: return work_layout(cfg->n_replicas, t.max_V, kStageNodes).total;
+        case LB_BUF_WORK:
+            return work_layout(cfg->n_replicas, t.max_V, kStageNodes, mark_chunks(cfg)).total;
         default: g_last_error = "unknown buffer id"; return 0;
     }
 }
@@ -658,8 +678,8 @@ void release(Context& c) {
     c.bead_ptrs = nullptr;
 }
 
-// enqueue one LB step on the context's streams (no graph)
-hipError_t enqueue_step(Context& c, int mode, int cur, hipStream_t main) {
+// enqueue one LB step on the context's streams (no graph); first/last: of the steps enqueued together
+hipError_t enqueue_step(Context& c, int mode, int cur, bool first, bool last, hipStream_t main) {
     void* src = c.pops[cur];
     void* dst = c.pops[1 - cur];
     if (mode == STEP_NO_HYDRO) {
@@ -670,6 +690,11 @@ hipError_t enqueue_step(Context& c, int mode, int cur, hipStream_t main) {
         return launch_bump(c, main);
     }
     const bool coupled = mode == STEP_COUPLED;
+    if (coupled && step_one_fits(c)) {
+        hipError_t e;
+        if (first && (e = launch_mark(c, cur, main)) != hipSuccess) return e;
+        return launch_step_one(c, cur, last, main);
+    }
     if (coupled && c.ntot_beads > 0) {
         // the bead work goes first: its workgroup needs nearly all of one compute unit's LDS,
         // and a sweep enqueued ahead of it fills every unit, so that the bead kernel would
@@ -707,7 +732,7 @@ int build_graph(Context& c, int mode, int parity, int len, hipGraphExec_t* out) 
     int cur = parity;
     hipError_t e = hipSuccess;
     for (int k = 0; k < len && e == hipSuccess; ++k) {
-        e = enqueue_step(c, mode, cur, c.cap);
+        e = enqueue_step(c, mode, cur, k == 0, k == len - 1, c.cap);
         if (mode != STEP_NO_HYDRO) cur = 1 - cur;
     }
     hipError_t e2 = hipStreamEndCapture(c.cap, &g);
@@ -842,7 +867,7 @@ int lb_init(const lbmd_config* cfg, const lbmd_buffers* bufs, void* hip_stream, 
     for (void* p : {c.pops[0], c.pops[1], c.beads, c.work})
         if (((uintptr_t)p & 255) != 0) return bail(fail(LB_EINVAL, "buffers must be 256-byte aligned"));
 
-    const WorkLayout W = work_layout((int)c.reps.size(), c.max_V, kStageNodes);
+    const WorkLayout W = work_layout((int)c.reps.size(), c.max_V, kStageNodes, mark_chunks(cfg));
     char* wb = (char*)c.work;
     c.d_reps = (Replica*)(wb + W.reps);
     c.d_state = (RunState*)(wb + W.state);
@@ -851,12 +876,19 @@ int lb_init(const lbmd_config* cfg, const lbmd_buffers* bufs, void* hip_stream, 
     c.d_stage = (double*)(wb + W.stage);
     c.stage_doubles = W.stage_doubles;
 
+    if (W.chunks > 0)
+        for (int k = 0; k < 2; ++k) {
+            c.marks[k].stamp = (long long*)(wb + W.stamps) + (size_t)k * W.chunks;
+            c.marks[k].mask = (unsigned long long*)(wb + W.masks) + (size_t)k * W.chunks;
+        }
+
     auto check = [&](hipError_t e, const char* what) -> int {
         if (e == hipSuccess) return LB_OK;
         return fail(e == hipErrorOutOfMemory ? LB_ENOMEM : LB_EDEVICE, std::string(what) + ": " + hipGetErrorString(e));
     };
     if ((rc = check(hipMemcpy(c.d_reps, c.reps.data(), sizeof(Replica) * c.reps.size(), hipMemcpyHostToDevice), "upload replicas")))
         return bail(rc);
+    if (W.chunks > 0 && (rc = check(hipMemset(wb + W.stamps, 0, W.total - W.stamps), "clear marks"))) return bail(rc);
     RunState st{};
     st.step = cfg->init ? cfg->init->step0 : 0;
     c.host_step = st.step;
@@ -971,8 +1003,8 @@ int lb_step(lbmd_ctx* ctx, int n_steps, unsigned flags) {
             done += len;
         }
     }
-    for (; done < n_steps; ++done) {
-        HIP_TRY(enqueue_step(c, mode, c.cur, c.stream));
+    for (const int begin = done; done < n_steps; ++done) {
+        HIP_TRY(enqueue_step(c, mode, c.cur, done == begin, done == n_steps - 1, c.stream));
         if (flips) c.cur = 1 - c.cur;
     }
     c.host_step += n_steps;

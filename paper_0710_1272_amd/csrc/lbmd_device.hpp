@@ -49,6 +49,14 @@ __host__ __device__ constexpr R w_of(int p) {
 // 16-bit deviation scale (power of two)
 __host__ __device__ constexpr float scale_of(int p) { return p == 0 ? 2.0f : (p <= 6 ? 16.0f : 32.0f); }
 
+__device__ __forceinline__ float fused(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fused(double a, double b, double c) { return __builtin_fma(a, b, c); }
+// x^2 + y^2 + z^2 in one fixed order of fused operations
+template <class R>
+__device__ __forceinline__ R sum_sq(R x, R y, R z) {
+    return fused(z, z, fused(x, x, y * y));
+}
+
 // ---------------------------------------------------------------------------------
 // Storage codecs.
 // ---------------------------------------------------------------------------------
@@ -432,7 +440,20 @@ struct RunState {
     long long step;  // LB step counter (Philox counter word)
     unsigned err;    // error word, LB_ERR_* bits
     unsigned pad;
+    long long step_of[2];  // the counter as the coupled steps of either buffer parity read it
 };
+
+// Nodes that the bead kernel updates itself (the nodes beads sit on, nearest-node coupling): it
+// has their populations in registers for the interpolation, collides them and adds the reaction,
+// so that no kernel has to follow the sweep to spread it.  The sweep leaves them alone.  Per 64
+// consecutive nodes of the box: the step the entry is for (plus one) and a bit per node.
+// Entries of other steps count for nothing, so nothing is cleared, and two copies alternate by
+// step, so that a step's beads can mark the next step's nodes while its sweep still reads.
+struct Marks {
+    long long* stamp = nullptr;  // null: no node is marked
+    unsigned long long* mask = nullptr;
+};
+__host__ __device__ inline long long mark_stamp(long long step) { return step + 1; }
 
 template <class Real>
 struct BeadPtrs {

@@ -87,6 +87,7 @@ struct Context {
     int obs_every = 0, obs_capacity = 0;  // observable record (0: none)
     std::vector<LatticeLaunch> lat_all;
     int md_lanes = 0;                  // lanes per bead of the bead kernel (0: by bead count)
+    Marks marks[2] = {};               // nodes the bead kernel updates itself, by buffer parity (null: none)
 
     bool use_graph = true;
     bool deterministic = false;        // LB_CFG_DETERMINISTIC
@@ -97,12 +98,20 @@ struct Context {
 
 // work-buffer layout (byte offsets), computed on the host
 struct WorkLayout {
-    size_t reps, state, partials, stage, prefix, total;
+    size_t reps, state, partials, stage, prefix, stamps, masks, total;
+    int chunks;  // 64-node chunks with marks (0: none)
     size_t stage_doubles;
     int partial_blocks;
     int n_prefix_tables;
 };
-WorkLayout work_layout(int n_reps, int max_V, long long max_stage_nodes);
+WorkLayout work_layout(int n_reps, int max_V, long long max_stage_nodes, int chunks);
+// Largest box of the one-launch step (k_step_one).  Its sweep runs at two waves a SIMD, which a bead
+// step of 33-40 us hides up to here: 128x128x80 (these 1.3e6 nodes) takes 38.7 us a step for 100 beads
+// in FP16 and 41.3 in FP32, against 44.9 and 61.8 as separate launches; 128x128x120 in FP16 with 20
+// beads 52.0 against 44.1.
+constexpr int kStepOneNodes = 5 << 18;
+// chunks with marks of a configuration: those of a box that may take the one-launch step, else 0
+int mark_chunks(const lbmd_config* cfg);
 
 // bead-buffer layout
 struct BeadLayout {
@@ -133,6 +142,12 @@ Replica make_replica(const lbmd_replica& in, size_t elem);
 // host-side checks of one replica's box, faces, walls, tau, rho0 and fluid_kT; "" if valid
 std::string replica_problem(const lbmd_replica& R);
 hipError_t launch_md(const Context& c, const void* cur, int mode, hipStream_t s);
+// One coupled step of one small box in one launch (cur: the buffer parity; last: the last step
+// before the state is looked at again).  launch_mark goes before the first of a run of such steps:
+// it marks that step's nodes and takes the step number.
+hipError_t launch_mark(const Context& c, int cur, hipStream_t s);
+bool step_one_fits(const Context& c);
+hipError_t launch_step_one(const Context& c, int cur, bool last, hipStream_t s);
 hipError_t launch_spread(const Context& c, void* dst, bool bump_step, hipStream_t s);
 hipError_t launch_bump(const Context& c, hipStream_t s);
 // one replica's bead state, coupling data or diagnostics, and the run state, written to pinned

@@ -16,21 +16,10 @@
 #pragma once
 
 #include <algorithm>
-#include <type_traits>
-#include <utility>
 
-#include "lbmd_internal.hpp"
+#include "lbmd_lattice.hpp"
 
 namespace lbmd {
-
-template <class F, int... Ps>
-__device__ __forceinline__ void md_for_pops_impl(F&& f, std::integer_sequence<int, Ps...>) {
-    (f(std::integral_constant<int, Ps>{}), ...);
-}
-template <class F>
-__device__ __forceinline__ void md_for_pops(F&& f) {
-    md_for_pops_impl(f, std::make_integer_sequence<int, Q>{});
-}
 
 template <int S>
 struct MDReal {
@@ -48,6 +37,13 @@ struct MDKArgs {
     BeadPtrs<Real> b;
     const void* cur;
     RunState* st;
+    const long long* step_at;  // the step counter this launch goes by
+    // one-launch step: the buffer it writes, the marks of this and of the next step (null: none to
+    // follow), the counter the next step goes by, and whether the run state's counter moves with it
+    void* dst;
+    Marks now, next;
+    long long* step_next;
+    int last;
     int mode;
     int nmax;
     int list_in_lds;
@@ -55,13 +51,12 @@ struct MDKArgs {
 };
 
 // nearest node: floor(r + 1/2); periodic axes wrap, free-slip axes clamp (NaN -> 0)
-__device__ __forceinline__ void ngp3(const Replica& R, const double* r, int* g) {
-    const int n[3] = {R.nx, R.ny, R.nz};
+__device__ __forceinline__ void ngp3(const int* n, const int* fs, const double* r, int* g) {
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         double t = floor(r[a] + 0.5);
         if (!(t >= -1e15 && t <= 1e15)) t = 0.0;  // non-finite
-        if (R.fs[a]) {
+        if (fs[a]) {
             t = t < 0.0 ? 0.0 : (t > n[a] - 1 ? (double)(n[a] - 1) : t);
         } else {
             t = t - n[a] * floor(t / n[a]);
@@ -78,6 +73,18 @@ struct Geom {
     int n_walls;
     int wall[LB_MAX_WALLS][6];
 };
+
+__device__ __forceinline__ bool is_solid(const Geom& G, int x, int y, int z) {
+    bool s = false;
+#pragma unroll
+    for (int k = 0; k < LB_MAX_WALLS; ++k) {
+        if (k >= G.n_walls) break;
+        const int* w = G.wall[k];
+        const bool pore = pore_open(w) && y >= w[2] && y <= w[3] && z >= w[4] && z <= w[5];
+        s = s || (x >= w[0] && x <= w[1] && !pore);
+    }
+    return s;
+}
 
 // A scalar the optimiser may not see through: what is computed from it is computed where it is
 // used instead of being held in registers across the substep loop.
@@ -164,7 +171,7 @@ __device__ __forceinline__ double wall_dist2(const Geom& G, const WallBounds& B,
     dv[0] = dx;
     dv[1] = dy;
     dv[2] = dz;
-    return dx * dx + dy * dy + dz * dz;
+    return sum_sq(dx, dy, dz);
 }
 
 // 1/x: the hardware reciprocal in FP32 (about 1 ulp), an exact division in FP64
@@ -199,7 +206,7 @@ template <class Real, class Raw>
 __device__ __forceinline__ void load_node(int storage, const Replica& R, const void* cur, const int* g, Raw* raw) {
     const PullMap map = make_pull_map(R, g[0], g[1], g[2]);
     long long off[Q];
-    md_for_pops([&](auto P) {
+    for_pops([&](auto P) {
         constexpr int p = decltype(P)::value;
         off[p] = R.pop_base + pull_element<p>(R, map);
     });
@@ -219,7 +226,7 @@ template <int S, class Real, class Raw>
 __device__ __forceinline__ void node_moments(Real rho0, const Raw* raw, Real* rho, Real* j) {
     using C = Codec<S>;
     Real m = 0, jx = 0, jy = 0, jz = 0;
-    md_for_pops([&](auto P) {
+    for_pops([&](auto P) {
         constexpr int p = decltype(P)::value;
         typename C::T e;
         if constexpr (sizeof(typename C::T) == 2) e = __builtin_bit_cast(typename C::T, (uint16_t)raw[p]);
@@ -255,6 +262,58 @@ __device__ __forceinline__ void node_velocity(int storage, Real rho0, const Raw*
     u[2] = j[2] / rho;
 }
 
+// The lattice update of one node from the elements load_node fetched, without the reaction:
+// what the sweep would store there.
+template <int S, class Raw>
+__device__ __forceinline__ void update_node(const Replica& R, const Raw* raw, void* dst, int node,
+                                            RunState* st) {
+    using C = Codec<S>;
+    typename C::R f[Q];
+    for_pops([&](auto P) {
+        constexpr int p = decltype(P)::value;
+        if constexpr (sizeof(typename C::T) == 2) f[p] = C::load_raw(__builtin_bit_cast(typename C::T, (uint16_t)raw[p]));
+        else f[p] = C::load_raw(__builtin_bit_cast(typename C::T, raw[p]));
+    });
+    relax_node<S, false>(R, f, node, st);
+    store_node<S, false>(R, f, (typename C::T*)dst, node);
+}
+
+// S_p = -(w_p / c_s^2) F . c_p with c_s^2 = 1/3, added to the populations at base (stride PS)
+template <int S>
+__device__ __forceinline__ void add_reaction(typename Codec<S>::T* __restrict__ base, long long PS,
+                                             const typename Codec<S>::R* F) {
+    using C = Codec<S>;
+    using Rl = typename C::R;
+    auto source = [&](auto P) {
+        constexpr int p = decltype(P)::value;
+        Rl fc = 0;
+        if constexpr (cx_of(p) != 0) fc += Rl(cx_of(p)) * F[0];
+        if constexpr (cy_of(p) != 0) fc += Rl(cy_of(p)) * F[1];
+        if constexpr (cz_of(p) != 0) fc += Rl(cz_of(p)) * F[2];
+        return -Rl(3) * w_of<Rl>(p) * fc;
+    };
+    if constexpr (S == LB_STORE_F32 || S == LB_STORE_F64) {
+        // full-precision storage: hardware float atomics without return (each node has one
+        // leader, so no two threads add to one element and the result is deterministic)
+        for_pops([&](auto P) {
+            constexpr int p = decltype(P)::value;
+            if constexpr (p != 0) (void)unsafeAtomicAdd(&base[(long long)p * PS], source(P));
+        });
+    } else {
+        // 16-bit storage: decode, add, re-encode; all 18 moving populations are read
+        // before any is written
+        Rl f[Q];
+        for_pops([&](auto P) {
+            constexpr int p = decltype(P)::value;
+            if constexpr (p != 0) f[p] = C::template load<p>(base[(long long)p * PS]);
+        });
+        for_pops([&](auto P) {
+            constexpr int p = decltype(P)::value;
+            if constexpr (p != 0) base[(long long)p * PS] = C::template store<p>(f[p] + source(P));
+        });
+    }
+}
+
 // One DPP lane exchange (no LDS round trip): quad_perm [1,0,3,2] swaps neighbouring lanes,
 // [2,3,0,1] swaps lane pairs, row_half_mirror reverses each group of 8 lanes, row_mirror
 // each row of 16.
@@ -282,13 +341,14 @@ __device__ __forceinline__ int dpp_x(int v) {
     return dpp_i<CTRL>(v);
 }
 
-// Sums of NV doubles over the block, valid in every thread; scratch: 16 NV doubles.  The wave's
+// Sums of NV doubles over the block's first `threads` threads (whole waves; the others have left),
+// valid in every one of them; scratch: 16 NV doubles.  The wave's
 // butterfly (partners 32, 16, 8, 4, 2, 1 lanes away) takes the last four from lane rotations
 // within rows of 16, which need no LDS round trip: after the first two exchanges every lane holds
 // the sum of its class modulo 16, and rotating by 8, 4, 2, 1 reaches the other half class.
 template <int NV>
-__device__ __forceinline__ void block_sums(double* vals, double* scratch) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
+__device__ __forceinline__ void block_sums(double* vals, double* scratch, int threads) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = (threads + 63) >> 6;
 #pragma unroll
     for (int k = 0; k < NV; ++k) vals[k] += __shfl_xor(vals[k], 32, 64);
 #pragma unroll
@@ -340,7 +400,7 @@ __device__ __forceinline__ Real separation_v(const double* ri, const double* pj,
     d[0] = (Real)dd[0];
     d[1] = (Real)dd[1];
     d[2] = (Real)dd[2];
-    return d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
+    return sum_sq(d[0], d[1], d[2]);
 }
 
 // Angular term of Sec. II at the middle bead of (a, b, c): V = kappa phi^2 / 2 with phi
@@ -520,6 +580,13 @@ __device__ __forceinline__ int build_list(int i, int n, bool bn, bool bp, const 
 // of interacting pairs is exactly that of the all-pairs definition.
 // Positions are double-buffered in LDS: one barrier per substep.  POLY compiles in the
 // angular term and rigid bonds (the kernel without them is the harmonic-chain model).
+// Every store of this wave has reached its XCD's L2 when this returns: after a barrier that
+// follows it, other waves of the workgroup may update the same memory there.
+__device__ __forceinline__ void stores_done() {
+    __threadfence_block();
+    __builtin_amdgcn_s_waitcnt(0);
+}
+
 // The kernel's first argument, read from the argument segment by a pointer that the optimiser
 // cannot tie to the argument it already holds.
 template <class Args>
@@ -529,18 +596,27 @@ __device__ __forceinline__ const Args& reread_args() {
     return *(const Args*)(const char*)p;
 }
 
-template <class Real, int G, int BPT, bool PERIODIC, int MAXT, bool POLY>
-__global__ __launch_bounds__(MAXT) void k_md(MDKArgs<Real> a, int storage) {
-    extern __shared__ __align__(16) double lds[];
+// threads: the block's threads that take part (whole waves)
+// OWN: the storage when the block also updates the nodes its beads sit on (one-launch step), else -1
+template <class Real, int G, int BPT, bool PERIODIC, int MAXT, bool POLY, int OWN = -1>
+__device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int storage, const int rep, const int threads,
+                                          double* lds) {
+    constexpr bool own_nodes = OWN >= 0;
     __shared__ double red[16 * 4];
-    const int NG = blockDim.x / G;  // groups per block
-    const Replica& R = a.reps[blockIdx.x];
+    const int NG = threads / G;  // groups
+    const Replica& R = a.reps[rep];
     const Geom GM = load_geom(R);
     const uint32_t seed_lo = R.seed_lo, seed_hi = R.seed_hi;
     const double xmid = R.xmid;
     const long long pop_base = R.pop_base;
     const int plane = R.S;
     const int n = R.n_beads;
+    const long long step = *a.step_at;
+    if (own_nodes && threadIdx.x == 0) {
+        // the counters the next step and the next call go by (nothing of this step reads them)
+        if (a.step_next) *a.step_next = step + 1;
+        if (a.last) a.st->step = step + 1;
+    }
     if (n == 0) return;
     const int b0 = R.bead0, NT = a.b.ntot, tid = threadIdx.x, nmax = a.nmax;
     const int grp = tid / G, gl = tid % G;
@@ -567,7 +643,6 @@ __global__ __launch_bounds__(MAXT) void k_md(MDKArgs<Real> a, int storage) {
     double* VXV = RW + 4 * nmax;
     PcrRow* PCRW = (PcrRow*)(RW + 7 * nmax);
     const int M = md.M;
-    const long long step = a.st->step;
     const int* nn = GM.n;
     const double nd[3] = {(double)GM.n[0], (double)GM.n[1], (double)GM.n[2]};
     const int per[3] = {GM.fs[0] ? 0 : 1, GM.fs[1] ? 0 : 1, GM.fs[2] ? 0 : 1};
@@ -582,7 +657,7 @@ __global__ __launch_bounds__(MAXT) void k_md(MDKArgs<Real> a, int storage) {
     // state and, with one bead per lane, the kept Verlet list (its length, the positions it
     // was built at, the first PF entries of each lane).  Whether the list is still valid is
     // known later; what was fetched in vain is dropped.
-    double* dg = a.b.diag + 8 * blockIdx.x;
+    double* dg = a.b.diag + 8 * rep;
     const double kept = dg[7];
     constexpr int PF = BPT == 1 ? (G == 1 ? 12 : (16 + G - 1) / G) : 1;
     double rref[BPT][3];
@@ -644,12 +719,8 @@ __global__ __launch_bounds__(MAXT) void k_md(MDKArgs<Real> a, int storage) {
                 for (int c = 0; c < 3; ++c) rref[k][c] = a.b.rref[c * NT + gi];
                 cnt[k] = a.b.ncount[gi];
             }
-            Real disp2 = 0;
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const Real dd = (Real)(r[k][c] - rref[k][c]);
-                disp2 += dd * dd;
-            }
+            const Real disp2 = sum_sq((Real)(r[k][0] - rref[k][0]), (Real)(r[k][1] - rref[k][1]),
+                                      (Real)(r[k][2] - rref[k][2]));
             moved |= !(disp2 <= hs2);
         }
         build = __builtin_amdgcn_readfirstlane(__syncthreads_or(moved)) != 0;
@@ -708,8 +779,8 @@ __global__ __launch_bounds__(MAXT) void k_md(MDKArgs<Real> a, int storage) {
 #pragma unroll
         for (int k = 0; k < BPT; ++k) {
             int g[3];
-            ngp3(R, r[k], g);
-            fluid[k] = own[k] && !is_solid(R, g[0], g[1], g[2]);
+            ngp3(GM.n, GM.fs, r[k], g);
+            fluid[k] = own[k] && !is_solid(GM, g[0], g[1], g[2]);
             node[k] = fluid[k] ? g[0] + GM.n[0] * (g[1] + GM.n[1] * g[2]) : -1;
             if (fluid[k]) load_node<Real>(storage, R, a.cur, g, raw[k]);
         }
@@ -718,6 +789,9 @@ __global__ __launch_bounds__(MAXT) void k_md(MDKArgs<Real> a, int storage) {
         for (int k = 0; k < BPT; ++k) {
             const int i = grp + k * NG;
             if (fluid[k]) node_velocity<Real>(storage, (Real)R.rho0, raw[k], u[k]);
+            if constexpr (own_nodes) {
+                if (fluid[k] && gl == 0) update_node<OWN>(R, raw[k], a.dst, node[k], a.st);
+            }
             if (own[k] && gl == 0) {
                 const int gi = b0 + i;
                 a.b.node[gi] = node[k];
@@ -1189,12 +1263,8 @@ __global__ __launch_bounds__(MAXT) void k_md(MDKArgs<Real> a, int storage) {
         bool moved = false;
 #pragma unroll
         for (int k = 0; k < BPT; ++k) {
-            Real disp2 = 0;
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const Real dd = (Real)(r[k][c] - rref[k][c]);
-                disp2 += dd * dd;
-            }
+            const Real disp2 = sum_sq((Real)(r[k][0] - rref[k][0]), (Real)(r[k][1] - rref[k][1]),
+                                      (Real)(r[k][2] - rref[k][2]));
             moved = moved | (own[k] & !(disp2 <= hs2));  // also catches a non-finite position
         }
         if (__ballot(moved) != 0ull && (tid & 63) == 0) vote[sub & 1] = ~sub;
@@ -1206,7 +1276,28 @@ __global__ __launch_bounds__(MAXT) void k_md(MDKArgs<Real> a, int storage) {
     // The arguments are read again from here on: held through the substeps, their pointers
     // push the loop's own scalars out of the scalar registers.
     const MDKArgs<Real>& E = reread_args<MDKArgs<Real>>();
-    double* dgE = E.b.diag + 8 * blockIdx.x;
+    double* dgE = E.b.diag + 8 * rep;
+    // The nodes of the next step, marked for its sweep in two passes (several beads may share
+    // a 64-node chunk): the chunk's entry is opened here, the bits follow below, after a barrier.
+    Marks next;
+    if constexpr (own_nodes) next = E.next;
+    int chunk[BPT];
+    unsigned long long bit[BPT];
+#pragma unroll
+    for (int k = 0; k < BPT; ++k) {
+        chunk[k] = -1;
+        bit[k] = 0;
+        if (!next.stamp || !own[k] || gl != 0) continue;
+        int g[3];
+        ngp3(GM.n, GM.fs, r[k], g);
+        if (is_solid(GM, g[0], g[1], g[2])) continue;
+        const int at = g[0] + GM.n[0] * (g[1] + GM.n[1] * g[2]);
+        chunk[k] = at >> 6;
+        bit[k] = 1ull << (at & 63);
+        next.stamp[chunk[k]] = mark_stamp(step + 1);
+        next.mask[chunk[k]] = 0;
+    }
+
     // keep the lists for the next launch when they were (re)built in this one
     if (builds > 0) {
 #pragma unroll
@@ -1244,10 +1335,12 @@ __global__ __launch_bounds__(MAXT) void k_md(MDKArgs<Real> a, int storage) {
         acc[2] += r[k][1];
         acc[3] += r[k][2];
     }
-    block_sums<4>(acc, red);
+    block_sums<4>(acc, red, threads);
 
     // one leader per occupied node (its lowest-index bead) sums the Fbar of the beads on
     // it in index order; a bead alone on its node is its own sum
+    bool lead_at[BPT];
+    Real lead_f[BPT][3];
     double* FX = P;  // positions are no longer needed
 #pragma unroll
     for (int k = 0; k < BPT; ++k) {
@@ -1298,6 +1391,20 @@ __global__ __launch_bounds__(MAXT) void k_md(MDKArgs<Real> a, int storage) {
 #pragma unroll
             for (int c = 0; c < 3; ++c) E.b.agg_f[c * NT + gi] = lead ? s[c] : Real(0);
         }
+        lead_at[k] = lead && gl == 0;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) lead_f[k][c] = s[c];
+    }
+    if constexpr (own_nodes) {
+        stores_done();
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < BPT; ++k) {
+            if (chunk[k] >= 0) atomicOr(&next.mask[chunk[k]], bit[k]);
+            if (!lead_at[k]) continue;
+            using T = typename Codec<OWN>::T;
+            add_reaction<OWN>((T*)E.dst + pop_base + node[k], plane, lead_f[k]);
+        }
     }
     if (tid == 0) {
         dgE[0] = acc[0];
@@ -1310,6 +1417,37 @@ __global__ __launch_bounds__(MAXT) void k_md(MDKArgs<Real> a, int storage) {
         if (builds > 0) dgE[7] = 1.0;
     }
     if (flags) atomicOr(&E.st->err, flags);
+}
+
+template <class Real, int G, int BPT, bool PERIODIC, int MAXT, bool POLY>
+__global__ __launch_bounds__(MAXT) void k_md(MDKArgs<Real> a, int storage) {
+    extern __shared__ __align__(16) double lds[];
+    bead_step<Real, G, BPT, PERIODIC, MAXT, POLY>(a, storage, blockIdx.x, blockDim.x, lds);
+}
+
+// A whole coupled step of one box in one launch: block 0 takes the bead step, which updates the
+// nodes its beads sit on (it has their populations for the interpolation) and adds the reaction
+// there; the others sweep every other node.  Nobody waits for anybody, so that the launch boundary
+// is the only ordering.  Bound by the bead step, a chain of latencies in one workgroup: as launches
+// of their own it, the sweep and the spread also paid for a dependency between two queues and for
+// the launch that followed (128x64x64, 100 beads, FP32: 45.3 us a step, here 40.0; rigid 74.4 and
+// 66.5; 12 beads in 48x24x24: 36.8 and 30.3).  The sweep runs with the bead step's registers, two
+// waves a SIMD, which it hides in a box this small.
+template <int S, class Real, int G, bool POLY>
+__global__ __launch_bounds__(512) void k_step_one(MDKArgs<Real> a, int bead_threads, int tiles) {
+    extern __shared__ __align__(16) double lds[];
+    if (blockIdx.x == 0) {
+        // the bead step is what the launch waits for
+        if ((int)threadIdx.x >= bead_threads) return;
+        __builtin_amdgcn_s_setprio(3);
+        bead_step<Real, G, 1, false, 512, POLY, S>(a, S, 0, bead_threads, lds);
+        return;
+    }
+    using T = typename Codec<S>::T;
+    const int tile = xcd_tile((int)blockIdx.x - 1, tiles, -1);
+    const long long step = *a.step_at;
+    sweep_node<S, false, false, true>(a.reps[0], tile * (int)blockDim.x + (int)threadIdx.x, MAP_FLAT, (const T*)a.cur,
+                                (T*)a.dst, a.st, a.now, mark_stamp(step));
 }
 
 // ---------------------------------------------------------------------------------
@@ -1351,9 +1489,9 @@ static inline size_t md_lds_bytes(const Context& c, int G) {
     return b;
 }
 
-template <class Real, int G, int BPT, bool PER, int MAXT, bool POLY>
-static hipError_t launch_md_t(const Context& c, const void* cur, int mode, int block, hipStream_t s) {
-    MDKArgs<Real> a;
+template <class Real>
+static inline MDKArgs<Real> md_args(const Context& c, const void* cur, int mode, int G) {
+    MDKArgs<Real> a{};
     a.reps = c.d_reps;
     a.md = c.md;
     a.b = *(const BeadPtrs<Real>*)c.bead_ptrs;
@@ -1363,6 +1501,13 @@ static hipError_t launch_md_t(const Context& c, const void* cur, int mode, int b
     a.nmax = md_nmax(c);
     a.list_in_lds = md_lists_in_lds(c) ? 1 : 0;
     a.noise_in_lds = md_noise_in_lds(c, G) ? 1 : 0;
+    a.step_at = &c.d_state->step;
+    return a;
+}
+
+template <class Real, int G, int BPT, bool PER, int MAXT, bool POLY>
+static hipError_t launch_md_t(const Context& c, const void* cur, int mode, int block, hipStream_t s) {
+    const MDKArgs<Real> a = md_args<Real>(c, cur, mode, G);
     const size_t lds = md_lds_bytes(c, G);
     static bool attr_set = false;
     if (!attr_set) {
@@ -1377,6 +1522,52 @@ static hipError_t launch_md_t(const Context& c, const void* cur, int mode, int b
     return hipGetLastError();
 }
 
+// threads of a workgroup of G lanes a bead for m beads
+static inline int md_block(int G, int m) { return std::min(1024, (G * m + 63) / 64 * 64); }
+
+template <int S, class Real, int G, bool POLY>
+static hipError_t launch_step_one_t(const Context& c, int cur, bool last, hipStream_t s) {
+    MDKArgs<Real> a = md_args<Real>(c, c.pops[cur], MD_COUPLED, G);
+    a.step_at = &c.d_state->step_of[cur];
+    a.dst = c.pops[1 - cur];
+    a.now = c.marks[cur];
+    if (!last) {
+        a.next = c.marks[1 - cur];
+        a.step_next = &c.d_state->step_of[1 - cur];
+    }
+    a.last = last ? 1 : 0;
+    static bool attr_set = false;
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute((const void*)k_step_one<S, Real, G, POLY>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - kMDStaticLds);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    // 512 threads whatever the beads need: the kernel's registers leave a compute unit two waves a
+    // SIMD, and a block of fewer waves than those eight would leave some of them unused
+    const int tiles = (c.reps[0].V + 511) / 512;
+    hipLaunchKernelGGL((k_step_one<S, Real, G, POLY>), dim3(1 + tiles), dim3(512), md_lds_bytes(c, G), s, a,
+                       md_block(G, std::max(c.max_beads, 1)), tiles);
+    return hipGetLastError();
+}
+
+// one step in one launch for the storage S; hipErrorNotSupported for other lanes per bead than
+// the 512-thread workgroups hold
+template <int S, bool POLY>
+hipError_t launch_step_one_g(const Context& c, int cur, bool last, hipStream_t s) {
+    using Real = typename MDReal<S>::type;
+    const int m = std::max(c.max_beads, 1);
+    const int G = c.md_lanes > 0 ? c.md_lanes : md_default_lanes(m);
+    if (md_block(G, m) > 512) return hipErrorNotSupported;
+    switch (G) {
+        case 16: return launch_step_one_t<S, Real, 16, POLY>(c, cur, last, s);
+        case 8: return launch_step_one_t<S, Real, 8, POLY>(c, cur, last, s);
+        case 4: return launch_step_one_t<S, Real, 4, POLY>(c, cur, last, s);
+        case 2: return launch_step_one_t<S, Real, 2, POLY>(c, cur, last, s);
+        default: return hipErrorNotSupported;
+    }
+}
+
 template <class Real, bool PER, bool POLY>
 hipError_t launch_md_g(const Context& c, const void* cur, int mode, hipStream_t s) {
     // G lanes per bead (the context's choice); with one lane per bead the 512-thread
@@ -1384,7 +1575,7 @@ hipError_t launch_md_g(const Context& c, const void* cur, int mode, hipStream_t 
     const int m = std::max(c.max_beads, 1);
     const int G = c.md_lanes > 0 ? c.md_lanes : md_default_lanes(m);
     if (!md_lanes_valid(G, m)) return hipErrorInvalidValue;
-    auto blk = [](int t) { return std::min(1024, (t + 63) / 64 * 64); };
+    auto blk = [](int t) { return md_block(1, t); };
     switch (G) {
         case 16: return launch_md_t<Real, 16, 1, PER, 512, POLY>(c, cur, mode, blk(16 * m), s);
         case 8: return launch_md_t<Real, 8, 1, PER, 512, POLY>(c, cur, mode, blk(8 * m), s);
@@ -1413,5 +1604,13 @@ extern template hipError_t launch_md_g<double, false, false>(const Context&, con
 extern template hipError_t launch_md_g<double, true, false>(const Context&, const void*, int, hipStream_t);
 extern template hipError_t launch_md_g<double, false, true>(const Context&, const void*, int, hipStream_t);
 extern template hipError_t launch_md_g<double, true, true>(const Context&, const void*, int, hipStream_t);
+extern template hipError_t launch_step_one_g<LB_STORE_F64, false>(const Context&, int, bool, hipStream_t);
+extern template hipError_t launch_step_one_g<LB_STORE_F64, true>(const Context&, int, bool, hipStream_t);
+extern template hipError_t launch_step_one_g<LB_STORE_F32, false>(const Context&, int, bool, hipStream_t);
+extern template hipError_t launch_step_one_g<LB_STORE_F32, true>(const Context&, int, bool, hipStream_t);
+extern template hipError_t launch_step_one_g<LB_STORE_F16DEV, false>(const Context&, int, bool, hipStream_t);
+extern template hipError_t launch_step_one_g<LB_STORE_F16DEV, true>(const Context&, int, bool, hipStream_t);
+extern template hipError_t launch_step_one_g<LB_STORE_BF16DEV, false>(const Context&, int, bool, hipStream_t);
+extern template hipError_t launch_step_one_g<LB_STORE_BF16DEV, true>(const Context&, int, bool, hipStream_t);
 
 }  // namespace lbmd

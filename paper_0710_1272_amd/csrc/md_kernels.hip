@@ -15,8 +15,7 @@ __global__ __launch_bounds__(256) void k_spread(const Replica* __restrict__ reps
                                                 BeadPtrs<typename MDReal<S>::type> b,
                                                 typename Codec<S>::T* __restrict__ dst, RunState* st,
                                                 int bump_step) {
-    using C = Codec<S>;
-    using Rl = typename C::R;
+    using Rl = typename Codec<S>::R;
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (bump_step && i == 0) st->step += 1;
     if (i >= b.ntot) return;
@@ -25,36 +24,7 @@ __global__ __launch_bounds__(256) void k_spread(const Replica* __restrict__ reps
     const long long PS = b.agg_at[b.ntot + i];
     const Rl F[3] = {(Rl)b.agg_f[i], (Rl)b.agg_f[b.ntot + i], (Rl)b.agg_f[2 * b.ntot + i]};
     if (at < 0) return;
-    typename C::T* __restrict__ base = dst + at;
-    // S_p = -(w_p / c_s^2) Fbar . c_p with c_s^2 = 1/3
-    auto source = [&](auto P) {
-        constexpr int p = decltype(P)::value;
-        Rl fc = 0;
-        if constexpr (cx_of(p) != 0) fc += Rl(cx_of(p)) * F[0];
-        if constexpr (cy_of(p) != 0) fc += Rl(cy_of(p)) * F[1];
-        if constexpr (cz_of(p) != 0) fc += Rl(cz_of(p)) * F[2];
-        return -Rl(3) * w_of<Rl>(p) * fc;
-    };
-    if constexpr (S == LB_STORE_F32 || S == LB_STORE_F64) {
-        // full-precision storage: hardware float atomics without return (each node has one
-        // leader, so no two threads add to one element and the result is deterministic)
-        md_for_pops([&](auto P) {
-            constexpr int p = decltype(P)::value;
-            if constexpr (p != 0) (void)unsafeAtomicAdd(&base[(long long)p * PS], source(P));
-        });
-    } else {
-        // 16-bit storage: decode, add, re-encode; all 18 moving populations are read
-        // before any is written
-        Rl f[Q];
-        md_for_pops([&](auto P) {
-            constexpr int p = decltype(P)::value;
-            if constexpr (p != 0) f[p] = C::template load<p>(base[(long long)p * PS]);
-        });
-        md_for_pops([&](auto P) {
-            constexpr int p = decltype(P)::value;
-            if constexpr (p != 0) base[(long long)p * PS] = C::template store<p>(f[p] + source(P));
-        });
-    }
+    add_reaction<S>(dst + at, PS, F);
 }
 
 __global__ void k_bump(RunState* st) { st->step += 1; }
@@ -85,6 +55,38 @@ __global__ __launch_bounds__(256) void k_readout(BeadPtrs<Real> b, const RunStat
         out[3 * (n + i) + c] = what == READ_BEADS ? (double)b.v[c * NT + g] : (double)b.fbar[c * NT + g];
     }
     if (what == READ_COUPLING) out[6 * n + i] = (double)b.node[g];
+}
+
+// Before a run of one-launch steps: the nodes of the
+// first step are marked for its sweep and the step counter is copied to where that step reads it.
+template <class Real>
+__global__ __launch_bounds__(256) void k_mark(const Replica* __restrict__ reps, BeadPtrs<Real> b,
+                                              const RunState* __restrict__ st, Marks marks, long long* step_of) {
+    const Replica& R = reps[0];
+    const long long step = st->step;
+    if (threadIdx.x == 0) *step_of = step;
+    const int n[3] = {R.nx, R.ny, R.nz}, fs[3] = {R.fs[0], R.fs[1], R.fs[2]};
+    const int nb = R.n_beads, b0 = R.bead0, NT = b.ntot;
+    for (int pass = 0; pass < 2; ++pass) {
+        for (int i = threadIdx.x; i < nb; i += blockDim.x) {
+            const double r[3] = {b.r[b0 + i], b.r[NT + b0 + i], b.r[2 * NT + b0 + i]};
+            int g[3];
+            ngp3(n, fs, r, g);
+            if (is_solid(R, g[0], g[1], g[2])) continue;
+            const int at = g[0] + R.nx * (g[1] + R.ny * g[2]);
+            const int c = at >> 6;
+            if (pass == 0) {
+                marks.stamp[c] = mark_stamp(step);
+                marks.mask[c] = 0;
+            } else {
+                atomicOr(&marks.mask[c], 1ull << (at & 63));
+            }
+        }
+        if (pass == 0) {
+            stores_done();
+            __syncthreads();
+        }
+    }
 }
 
 // Observable record of the translocation analysis (Sec. III), one workgroup per replica,
@@ -145,7 +147,7 @@ __global__ __launch_bounds__(256) void k_observe(const Replica* __restrict__ rep
             o[11] += d2;
         }
     }
-    block_sums<12>(o, red);
+    block_sums<12>(o, red, blockDim.x);
     if (threadIdx.x != 0) return;
     double* rec = b.obs + (size_t)blockIdx.x * ((size_t)b.obs_cap + 1) * 8;
     const double cnt = rec[0];
@@ -273,7 +275,7 @@ __global__ __launch_bounds__(256) void k_spread_tri(const Replica* __restrict__ 
         if (is_solid(R, g[0], g[1], g[2])) return;
         const Rl w = (Rl)(w1[0][c & 1] * w1[1][(c >> 1) & 1] * w1[2][(c >> 2) & 1]);
         typename C::T* base = dst + R.pop_base + g[0] + (long long)R.nx * (g[1] + (long long)R.ny * g[2]);
-        md_for_pops([&](auto P) {
+        for_pops([&](auto P) {
             constexpr int p = decltype(P)::value;
             if constexpr (p != 0) {
                 Rl fc = 0;
@@ -349,7 +351,7 @@ __global__ __launch_bounds__(64) void k_spread_tri_fx(const Replica* __restrict_
             flags |= LB_ERR_NONFINITE;
             break;
         }
-        md_for_pops([&](auto P) {
+        for_pops([&](auto P) {
             constexpr int p = decltype(P)::value;
             if constexpr (p != 0) {
                 double fc = 0.0;
@@ -386,7 +388,7 @@ __global__ __launch_bounds__(256) void k_spread_fx_apply(const Replica* __restri
     if (key == 0ull) return;
     const long long PS = reps[b.hrep[h]].S;  // population plane stride
     typename C::T* __restrict__ base = dst + (long long)(key - 1ull);
-    md_for_pops([&](auto P) {
+    for_pops([&](auto P) {
         constexpr int p = decltype(P)::value;
         if constexpr (p != 0) {
             long long* cell = &b.hsum[(size_t)(p - 1) * b.hcap + h];
@@ -443,6 +445,46 @@ static hipError_t launch_md_r(const Context& c, const void* cur, int mode, hipSt
 hipError_t launch_md(const Context& c, const void* cur, int mode, hipStream_t s) {
     if (c.storage == LB_STORE_F64) return launch_md_r<double>(c, cur, mode, s);
     return launch_md_r<float>(c, cur, mode, s);
+}
+
+// One lane a bead (more than 256 beads by default) stays with separate launches: the bead step then
+// needs every register, and beside the sweep's code it spills (400 beads in 96x48x48, FP32: 90.9 us a
+// step in one launch, 83.8 apart; 200 beads, two lanes each: 54.6 and 59.2; 100 beads in 128x64x64:
+// 40.0 and 45.3, rigid 66.5 and 74.4; 12 beads in 48x24x24: 30.3 and 36.8).
+bool step_one_fits(const Context& c) {
+    if (!c.marks[0].stamp || c.obs_every > 0) return false;
+    const int m = std::max(c.max_beads, 1);
+    const int G = c.md_lanes > 0 ? c.md_lanes : md_default_lanes(m);
+    return G > 1 && md_block(G, m) <= 512;
+}
+
+hipError_t launch_step_one(const Context& c, int cur, bool last, hipStream_t s) {
+    const bool poly = c.md.rigid || c.md.kappa_phi != 0.0;
+    switch (c.storage) {
+        case LB_STORE_F64:
+            return poly ? launch_step_one_g<LB_STORE_F64, true>(c, cur, last, s) : launch_step_one_g<LB_STORE_F64, false>(c, cur, last, s);
+        case LB_STORE_F32:
+            return poly ? launch_step_one_g<LB_STORE_F32, true>(c, cur, last, s) : launch_step_one_g<LB_STORE_F32, false>(c, cur, last, s);
+        case LB_STORE_F16DEV:
+            return poly ? launch_step_one_g<LB_STORE_F16DEV, true>(c, cur, last, s)
+                        : launch_step_one_g<LB_STORE_F16DEV, false>(c, cur, last, s);
+        case LB_STORE_BF16DEV:
+            return poly ? launch_step_one_g<LB_STORE_BF16DEV, true>(c, cur, last, s)
+                        : launch_step_one_g<LB_STORE_BF16DEV, false>(c, cur, last, s);
+        default: return hipErrorNotSupported;
+    }
+}
+
+template <class Real>
+static hipError_t launch_mark_t(const Context& c, int cur, hipStream_t s) {
+    const BeadPtrs<Real> b = *(const BeadPtrs<Real>*)c.bead_ptrs;
+    hipLaunchKernelGGL((k_mark<Real>), dim3(1), dim3(256), 0, s, c.d_reps, b, c.d_state,
+                       c.marks[cur], &c.d_state->step_of[cur]);
+    return hipGetLastError();
+}
+
+hipError_t launch_mark(const Context& c, int cur, hipStream_t s) {
+    return c.storage == LB_STORE_F64 ? launch_mark_t<double>(c, cur, s) : launch_mark_t<float>(c, cur, s);
 }
 
 template <int S>

@@ -35,7 +35,7 @@ COPIES = 4
 
 def kernel_source_hash() -> str:
     h = hashlib.sha256()
-    for name in ("lb_kernels.hip", "lbmd_device.hpp"):
+    for name in ("lb_kernels.hip", "lbmd_lattice.hpp", "lbmd_device.hpp"):
         with open(os.path.join(ROOT, "paper_0710_1272_amd", "csrc", name), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
