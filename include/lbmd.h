@@ -341,7 +341,7 @@ int lb_block_size(const lbmd_ctx* ctx);
 /* Lattice-kernel launch shape in use: threads per block, LB_MAP_FLAT/ROWS/SHIFTED/FLAT2, the XCD
  * tile order (LB_XCD_HARDWARE, LB_XCD_CONTIGUOUS or a chunk size) and whether the
  * populations are written with non-temporal stores (1: both buffers together exceed
- * 160 MB, so they are streamed past the last-level cache; 0: they stay cached between
+ * 340 MB, so they are streamed past the last-level cache; 0: they stay cached between
  * steps).  Any pointer may be NULL.  Returns LB_OK or LB_EINVAL for a NULL context. */
 int lb_launch_shape(const lbmd_ctx* ctx, int* block, int* mapping, int* xcd_order, int* nt_stores);
 

@@ -946,9 +946,12 @@ int lb_init(const lbmd_config* cfg, const lbmd_buffers* bufs, void* hip_stream, 
     else if (cfg->xcd_order == LB_XCD_CONTIGUOUS) c.lat_chunk = -1;
     else c.lat_chunk = cfg->xcd_order;
     if ((rc = set_lattice_shape(c, cfg->block_size ? cfg->block_size : 256))) return bail(rc);
-    // both population buffers within 160 MB stay in the 256 MB last-level cache between
-    // sweeps when stored normally; larger ones are streamed past it
-    c.lat_nt = 2.0 * (double)c.pop_elems * (double)store_size(c.storage) > 160e6;
+    // Both population buffers stay in the 256 MB last-level cache between sweeps when stored
+    // normally, and a good part of somewhat larger ones does; beyond that they are streamed past it.
+    // A lattice step of one box, stored normally / streamed, us: 174 MB 30.5 / 38.4, 224 MB
+    // 38.0 / 50.9, 261 MB 43.3 / 54.8, 299 MB 56.8 / 59.7 (FP32); 319 MB 63.2 / 67.2 (FP16) and
+    // 60.8 / 64.5 (FP64); 398 MB 86.0 / 84.4 (FP16) and 83.1 / 81.2 (FP64); 598 MB 117.6 / 114.6.
+    c.lat_nt = 2.0 * (double)c.pop_elems * (double)store_size(c.storage) > 340e6;
 
     if ((rc = check(hipStreamCreateWithFlags(&c.side, hipStreamNonBlocking), "side stream"))) return bail(rc);
     if ((rc = check(hipStreamCreateWithFlags(&c.cap, hipStreamNonBlocking), "capture stream"))) return bail(rc);
