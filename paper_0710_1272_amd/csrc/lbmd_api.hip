@@ -831,6 +831,7 @@ int lb_init(const lbmd_config* cfg, const lbmd_buffers* bufs, void* hip_stream, 
     const double skin = 1.0;
     md.rl2 = (std::sqrt(md.rc2) + skin + 1e-3) * (std::sqrt(md.rc2) + skin + 1e-3);
     md.half_skin2 = 0.25 * skin * skin;
+    md.rin2 = (std::sqrt(md.rc2) + kInnerSkin + 1e-3) * (std::sqrt(md.rc2) + kInnerSkin + 1e-3);
     md.zone = md.rcw + std::sqrt(md.half_skin2) + 1e-3;
     // two beads on one node are at most sqrt(3) apart (the node's unit cell); a kept list
     // holds every non-bonded pair closer than rc, so it names them only when rc covers that

@@ -11,6 +11,8 @@
 
 namespace lbmd {
 
+constexpr double kInnerSkin = 0.4;  // of the bead kernel's inner lists
+
 // Scalar bead-model parameters as the MD kernel uses them.
 struct MDDev {
     int M;
@@ -20,6 +22,7 @@ struct MDDev {
     double eps, sigma2, rc2;          // WCA bead-bead: rc^2 = 2^(1/3) sigma^2
     double eps_w, sigma_w2, rcw2, rcw; // WCA bead-surface
     double rl2, half_skin2;           // Verlet list radius^2 (rc + skin)^2 and (skin/2)^2
+    double rin2;                      // inner list radius^2 (rc + kInnerSkin)^2
     double zone;                      // reach of the surface terms plus what a bead moves between builds
     int node_scan_all;                // 1: find the beads sharing a node by scanning every bead
                                       // (the WCA cutoff is shorter than a node cell's diagonal

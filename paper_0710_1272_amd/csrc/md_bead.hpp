@@ -493,8 +493,18 @@ __device__ __forceinline__ double pcr_solve(PcrRow* W, int nmax, int m, int t, d
 // (fewer under the 1024-thread bound, where registers are scarcer)
 template <int G, int BPT, int MAXT>
 struct SlotsPerLane {
-    static constexpr int K = MAXT > 512 ? (BPT > 1 ? 1 : 2) : (BPT > 1 ? 4 : (G >= 8 ? 1 : 8 / G));
+    // One lane a bead below the 1024-thread bound (257 to 512 beads): the substeps go by a shorter
+    // inner list.  More lanes hold a bead's entries in their slots already; beyond 512 beads there
+    // are no registers left for the second reference position.
+    static constexpr bool inner = G == 1 && BPT == 1 && MAXT <= 512;
+    static constexpr int K = MAXT > 512 ? (BPT > 1 ? 1 : 2) : (BPT > 1 ? 4 : (G >= 8 ? 1 : inner ? 6 : 8 / G));
 };
+// Inner list: the entries of the Verlet list closer than rc + kInnerSkin, in the list's order, taken
+// again when a bead has moved kInnerSkin / 2 since.  A lane runs through its entries one after the
+// other and a wave through its longest lane: 8 to 13 list entries a bead are 3 to 5 inner ones.  The
+// entries left out would add zeros, so the sums stay what they are.  400 beads (256x128x128, FP16):
+// the bead kernel 86 -> 68 us, the step 119 -> 95.5.
+constexpr int kInnerMax = 16;  // entries held; a bead with more goes by the Verlet list
 
 // Verlet list of bead i (group of G lanes): every non-bonded bead closer than the list
 // radius, in lane-then-index order.  Returns the count (may exceed the capacity).
@@ -629,8 +639,11 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
     unsigned short* GL = a.b.nlist + b0;
     const bool list_lds = a.list_in_lds != 0;
     auto list_at = [&](int q, int i) -> int { return list_lds ? LL[q * nmax + i] : GL[(size_t)q * NT + i]; };
-    // random forces [M][nmax][3], after the lists (or after BN when the lists are global)
-    Real* NZ = (Real*)(BN + nmax + (list_lds ? (size_t)kNeighbourMax * nmax * 2 : (size_t)0));
+    // inner lists [kInnerMax][nmax] and random forces [M][nmax][3], after the lists (or after BN
+    // when the lists are global)
+    unsigned short* IL = (unsigned short*)(BN + nmax + (list_lds ? (size_t)kNeighbourMax * nmax * 2 : (size_t)0));
+    constexpr bool INNER = SlotsPerLane<G, BPT, MAXT>::inner;
+    Real* NZ = (Real*)(IL + (INNER ? kInnerMax * nmax : 0));
     const bool noise_lds = G > 1 && a.noise_in_lds;
     const MDDev md = a.md;
     // rigid bonds: SHAKE/RATTLE work area after the random-force table, doubles:
@@ -823,8 +836,8 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
     // divergent in the compiler's eyes, and every decision of the loop a vector branch).
     // Two words, so that one barrier per substep separates the writes of a substep from its
     // reads and from the next writes to the same word; nothing has to be cleared.
-    __shared__ int vote[2], shake_vote[2];
-    if (tid < 2) vote[tid] = shake_vote[tid] = 0;
+    __shared__ int vote[2], inner_vote[2], shake_vote[2];
+    if (tid < 2) vote[tid] = inner_vote[tid] = shake_vote[tid] = 0;
     int votes = 0;  // rigid bonds: convergence votes taken
     __syncthreads();
 
@@ -854,6 +867,15 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
     const double zone = md.zone;
     bool near_wall[BPT][LB_MAX_WALLS], near_face[BPT];  // of any bead of the wave
     bool more[BPT];  // whether any bead of the wave has list entries beyond the register slots
+    int cin[BPT];    // entries the substeps go through: of the inner list, or of the Verlet list
+    bool half[BPT];  // inner list: whether any bead of the wave has entries in the slots' upper half
+    double iref[BPT][3];  // where the inner list was taken
+    const Real rin2 = (Real)md.rin2;
+    const Real his2 = (Real)(0.25 * kInnerSkin * kInnerSkin);
+    auto entry_at = [&](int q, int i, int k) -> int {
+        if constexpr (INNER) return cin[k] <= kInnerMax ? (int)IL[q * nmax + i] : list_at(q, i);
+        else return list_at(q, i);
+    };
     WallBounds WB[LB_MAX_WALLS];
 #pragma unroll
     for (int w = 0; w < LB_MAX_WALLS; ++w) WB[w] = wall_bounds(GM.wall[w]);
@@ -878,14 +900,19 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
 #pragma unroll
             for (int k = 0; k < BPT; ++k)
 #pragma unroll
-                for (int s = 0; s < K; ++s)
+                for (int s = 0; s < K; ++s) {
+                    if (INNER && s == K / 2 && !half[k]) break;
 #pragma unroll
                     for (int c = 0; c < 3; ++c) pj[k][s][c] = PB[slot3[k][s] + c];
+                }
         };
+        bool refresh = sub == 0;
         if (sub > 0) {
             const int voted = vote[(sub - 1) & 1];
+            const int inner_voted = INNER ? inner_vote[(sub - 1) & 1] : 0;
             read_slots();
             build = __builtin_amdgcn_readfirstlane(voted) == -sub;  // ~(sub - 1)
+            if (INNER) refresh = __builtin_amdgcn_readfirstlane(inner_voted) == -sub;
         }
         if (build) {
             ++builds;
@@ -905,7 +932,7 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
             }
             __syncthreads();
         }
-        if (build || sub == 0) {
+        if (build || refresh) {
 #pragma unroll
             for (int k = 0; k < BPT; ++k) {
                 const int i = grp + k * NG;
@@ -921,14 +948,44 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
                 for (int c = 0; c < 3; ++c)
                     if (GM.fs[c]) f_near = f_near || !(r[k][c] + 0.5 >= zone && (nn[c] - 0.5) - r[k][c] >= zone);
                 near_face[k] = __ballot(own[k] && f_near) != 0ull;
+                cin[k] = cnt[k];
+                if constexpr (INNER) {
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) iref[k][c] = r[k][c];
+                    if (own[k] && cnt[k] <= kNeighbourMax) {
+                        int m = 0;
+                        constexpr int U = 4;
+                        for (int q0 = 0; q0 < cnt[k]; q0 += U) {
+                            int j[U];
+                            double pq[U][3];
+#pragma unroll
+                            for (int t = 0; t < U; ++t) j[t] = q0 + t < cnt[k] ? list_at(q0 + t, i) : i;
+#pragma unroll
+                            for (int t = 0; t < U; ++t)
+#pragma unroll
+                                for (int c = 0; c < 3; ++c) pq[t][c] = PB[3 * j[t] + c];
+#pragma unroll
+                            for (int t = 0; t < U; ++t) {
+                                Real d[3];
+                                if (q0 + t < cnt[k] && separation_v<Real, PERIODIC>(r[k], pq[t], per, nd, d) < rin2) {
+                                    if (m < kInnerMax) IL[m * nmax + i] = (unsigned short)j[t];
+                                    ++m;
+                                }
+                            }
+                        }
+                        if (m <= kInnerMax) cin[k] = m;
+                        // a bead with more entries goes by the Verlet list, which is longer still
+                    }
+                }
 #pragma unroll
                 for (int s = 0; s < K; ++s) {
                     const int q = gl + s * G;
-                    used[k][s] = own[k] && cnt[k] <= kNeighbourMax && q < cnt[k];
+                    used[k][s] = own[k] && cnt[k] <= kNeighbourMax && q < cin[k];
                     // an unused slot reads the bead itself
-                    slot3[k][s] = 3 * (used[k][s] ? list_at(q, i) : own[k] ? i : 0);
+                    slot3[k][s] = 3 * (used[k][s] ? entry_at(q, i, k) : own[k] ? i : 0);
                 }
-                more[k] = __ballot(own[k] && cnt[k] > K * G) != 0ull;
+                half[k] = __ballot(own[k] && cin[k] > K / 2 * G) != 0ull;
+                more[k] = __ballot(own[k] && cin[k] > K * G) != 0ull;
             }
             read_slots();
         }
@@ -998,13 +1055,16 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
                 fz += c * d[2];
             };
 #pragma unroll
-            for (int s = 0; s < K; ++s) pair(pj[k][s], used[k][s]);
+            for (int s = 0; s < K; ++s) {
+                if (INNER && s == K / 2 && !half[k]) break;
+                pair(pj[k][s], used[k][s]);
+            }
             if (more[k]) {
                 // entries beyond the register slots, U a lane and round: a round, not an entry,
                 // costs the two LDS round trips (entry, position)
                 constexpr int U = G == 1 ? 4 : 2;
                 const bool overflow = cnt[k] > kNeighbourMax;
-                const int lim = own[k] ? (overflow ? n : cnt[k]) : 0;
+                const int lim = own[k] ? (overflow ? n : cin[k]) : 0;
                 for (int q0 = overflow ? gl : gl + K * G; q0 < lim; q0 += U * G) {
                     int j[U];
                     bool ok[U];
@@ -1013,7 +1073,7 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
                     for (int t = 0; t < U; ++t) {
                         const int q = q0 + t * G;
                         ok[t] = q < lim;
-                        j[t] = !ok[t] ? i : overflow ? q : list_at(q, i);
+                        j[t] = !ok[t] ? i : overflow ? q : entry_at(q, i, k);
                     }
 #pragma unroll
                     for (int t = 0; t < U; ++t) {
@@ -1260,13 +1320,19 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
                 }
             }
         }
-        bool moved = false;
+        bool moved = false, inner_moved = false;
 #pragma unroll
         for (int k = 0; k < BPT; ++k) {
             const Real disp2 = sum_sq((Real)(r[k][0] - rref[k][0]), (Real)(r[k][1] - rref[k][1]),
                                       (Real)(r[k][2] - rref[k][2]));
             moved = moved | (own[k] & !(disp2 <= hs2));  // also catches a non-finite position
+            if constexpr (INNER) {
+                const Real in2 = sum_sq((Real)(r[k][0] - iref[k][0]), (Real)(r[k][1] - iref[k][1]),
+                                        (Real)(r[k][2] - iref[k][2]));
+                inner_moved = inner_moved | (own[k] & !(in2 <= his2));
+            }
         }
+        if (INNER && __ballot(inner_moved) != 0ull && (tid & 63) == 0) inner_vote[sub & 1] = ~sub;
         if (__ballot(moved) != 0ull && (tid & 63) == 0) vote[sub & 1] = ~sub;
         __syncthreads();
         cur = 3 * nmax - cur;
@@ -1483,10 +1549,11 @@ static inline bool md_noise_in_lds(const Context& c, int G) {
 
 static inline size_t md_lds_bytes(const Context& c, int G) {
     const size_t nmax = (size_t)md_nmax(c);
+    const size_t inner = G == 1 && c.max_beads <= 512 ? nmax * kInnerMax * sizeof(unsigned short) : 0;
     size_t b = md_base_lds(nmax) + md_rigid_lds(c, nmax);
     if (md_lists_in_lds(c)) b += md_list_lds(nmax);
     if (md_noise_in_lds(c, G)) b += md_noise_lds(c, nmax);
-    return b;
+    return b + inner;
 }
 
 template <class Real>
