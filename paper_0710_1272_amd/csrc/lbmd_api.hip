@@ -678,13 +678,22 @@ void release(Context& c) {
     c.bead_ptrs = nullptr;
 }
 
-// enqueue one LB step on the context's streams (no graph); first/last: of the steps enqueued together
-hipError_t enqueue_step(Context& c, int mode, int cur, bool first, bool last, hipStream_t main) {
+// enqueue one LB step on the context's streams (no graph): the k-th of len enqueued together
+hipError_t enqueue_step(Context& c, int mode, int cur, int k, int len, hipStream_t main) {
     void* src = c.pops[cur];
     void* dst = c.pops[1 - cur];
     if (mode == STEP_NO_HYDRO) {
-        // beads alone; the counter moves in its own launch, after every replica has read it
         hipError_t e;
+        if (c.ntot_beads > 0 && c.obs_every == 0 && len > 1) {
+            // Every workgroup reads the counter, so that no launch may move the one it reads: the
+            // steps hand it on in two words used in turn, and the last one moves the run state's.
+            // As a launch of its own behind every step the counter took 5 us of a step of 40.
+            long long* of = c.d_state->step_of;
+            const bool last = k == len - 1;
+            const StepCount at{k == 0 ? nullptr : &of[k & 1], last ? nullptr : &of[(k + 1) & 1], last};
+            return launch_md(c, src, MD_SUBSTEPS | MD_NO_HYDRO, main, at);
+        }
+        // beads alone; the counter moves in its own launch, after every replica has read it
         if (c.ntot_beads > 0 && (e = launch_md(c, src, MD_SUBSTEPS | MD_NO_HYDRO, main)) != hipSuccess) return e;
         if (c.ntot_beads > 0 && c.obs_every > 0 && (e = launch_observe(c, true, main)) != hipSuccess) return e;
         return launch_bump(c, main);
@@ -692,8 +701,8 @@ hipError_t enqueue_step(Context& c, int mode, int cur, bool first, bool last, hi
     const bool coupled = mode == STEP_COUPLED;
     if (coupled && step_one_fits(c)) {
         hipError_t e;
-        if (first && (e = launch_mark(c, cur, main)) != hipSuccess) return e;
-        return launch_step_one(c, cur, last, main);
+        if (k == 0 && (e = launch_mark(c, cur, main)) != hipSuccess) return e;
+        return launch_step_one(c, cur, k == len - 1, main);
     }
     if (coupled && c.ntot_beads > 0) {
         // the bead work goes first: its workgroup needs nearly all of one compute unit's LDS,
@@ -732,7 +741,7 @@ int build_graph(Context& c, int mode, int parity, int len, hipGraphExec_t* out) 
     int cur = parity;
     hipError_t e = hipSuccess;
     for (int k = 0; k < len && e == hipSuccess; ++k) {
-        e = enqueue_step(c, mode, cur, k == 0, k == len - 1, c.cap);
+        e = enqueue_step(c, mode, cur, k, len, c.cap);
         if (mode != STEP_NO_HYDRO) cur = 1 - cur;
     }
     hipError_t e2 = hipStreamEndCapture(c.cap, &g);
@@ -1008,7 +1017,7 @@ int lb_step(lbmd_ctx* ctx, int n_steps, unsigned flags) {
         }
     }
     for (const int begin = done; done < n_steps; ++done) {
-        HIP_TRY(enqueue_step(c, mode, c.cur, done == begin, done == n_steps - 1, c.stream));
+        HIP_TRY(enqueue_step(c, mode, c.cur, done - begin, n_steps - begin, c.stream));
         if (flips) c.cur = 1 - c.cur;
     }
     c.host_step += n_steps;

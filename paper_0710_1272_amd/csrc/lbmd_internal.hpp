@@ -144,7 +144,14 @@ hipError_t launch_conserved_desc(const Replica& R, int storage, const void* src,
 Replica make_replica(const lbmd_replica& in, size_t elem);
 // host-side checks of one replica's box, faces, walls, tau, rho0 and fluid_kT; "" if valid
 std::string replica_problem(const lbmd_replica& R);
-hipError_t launch_md(const Context& c, const void* cur, int mode, hipStream_t s);
+// The step counter of one of several steps enqueued together: where its launch reads it (null: the run
+// state), where it leaves the next step's (null: nowhere), whether it moves the run state's.
+struct StepCount {
+    const long long* read = nullptr;
+    long long* next = nullptr;
+    bool last = false;
+};
+hipError_t launch_md(const Context& c, const void* cur, int mode, hipStream_t s, const StepCount& at = StepCount{});
 // One coupled step of one small box in one launch (cur: the buffer parity; last: the last step
 // before the state is looked at again).  launch_mark goes before the first of a run of such steps:
 // it marks that step's nodes and takes the step number.

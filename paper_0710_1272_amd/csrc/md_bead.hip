@@ -7,5 +7,6 @@
 #endif
 
 namespace lbmd {
-template hipError_t launch_md_g<MD_REAL, MD_PERIODIC != 0, MD_POLY != 0>(const Context&, const void*, int, hipStream_t);
+template hipError_t launch_md_g<MD_REAL, MD_PERIODIC != 0, MD_POLY != 0>(const Context&, const void*, int, const StepCount&,
+                                                                         hipStream_t);
 }  // namespace lbmd

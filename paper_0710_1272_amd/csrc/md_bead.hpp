@@ -40,12 +40,14 @@ struct MDKArgs {
     const void* cur;
     RunState* st;
     const long long* step_at;  // the step counter this launch goes by
-    // one-launch step: the buffer it writes, the marks of this and of the next step (null: none to
-    // follow), the counter the next step goes by, and whether the run state's counter moves with it
-    void* dst;
-    Marks now, next;
+    // the counter the next step goes by (null: none that this launch sets), and whether the run
+    // state's counter moves with this step
     long long* step_next;
     int last;
+    // one-launch step: the buffer it writes, the marks of this and of the next step (null: none to
+    // follow)
+    void* dst;
+    Marks now, next;
     int mode;
     int nmax;
     int list_in_lds;
@@ -640,7 +642,7 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
     const int plane = R.S;
     const int n = R.n_beads;
     const long long step = *a.step_at;
-    if (own_nodes && threadIdx.x == 0) {
+    if (rep == 0 && threadIdx.x == 0) {
         // the counters the next step and the next call go by (nothing of this step reads them)
         if (a.step_next) *a.step_next = step + 1;
         if (a.last) a.st->step = step + 1;
@@ -894,13 +896,9 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
         if constexpr (INNER) return cin[k] <= kInnerMax ? (int)IL[q * nmax + i] : list_at(q, i);
         else return list_at(q, i);
     };
-    WallInts WI[LB_MAX_WALLS];
     WallBounds WB[LB_MAX_WALLS];
 #pragma unroll
-    for (int w = 0; w < LB_MAX_WALLS; ++w) {
-        WI[w] = wall_ints(GM, GM.wall[w]);
-        WB[w] = wall_bounds(WI[w]);
-    }
+    for (int w = 0; w < LB_MAX_WALLS; ++w) WB[w] = wall_bounds(wall_ints(GM, GM.wall[w]));
 #pragma unroll
     for (int k = 0; k < BPT; ++k) {
         const int i = own[k] ? grp + k * NG : 0;
@@ -1167,12 +1165,10 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
                     // solve out of the registers)
                     WallBounds B = WB[w];
                     if (POLY) {
-                        WallInts I = WI[w];
+                        int wl[6];
 #pragma unroll
-                        for (int m = 0; m < 6; ++m) I.side[m] = here(I.side[m]);
-#pragma unroll
-                        for (int a = 0; a < 3; ++a) I.lo[a] = here(I.lo[a]), I.hi1[a] = here(I.hi1[a]);
-                        B = wall_bounds(I);
+                        for (int m = 0; m < 6; ++m) wl[m] = here(GM.wall[w][m]);
+                        B = wall_bounds(wall_ints(GM, wl));
                     }
                     const double q = wall_dist2<PERIODIC>(GM, B, r[k], xw, dv);
                     const bool closer = w == 0 || q < best2;
@@ -1594,7 +1590,7 @@ static inline size_t md_lds_bytes(const Context& c, int G) {
 }
 
 template <class Real>
-static inline MDKArgs<Real> md_args(const Context& c, const void* cur, int mode, int G) {
+static inline MDKArgs<Real> md_args(const Context& c, const void* cur, int mode, int G, const StepCount& at = StepCount{}) {
     MDKArgs<Real> a{};
     a.reps = c.d_reps;
     a.md = c.md;
@@ -1605,13 +1601,16 @@ static inline MDKArgs<Real> md_args(const Context& c, const void* cur, int mode,
     a.nmax = md_nmax(c);
     a.list_in_lds = md_lists_in_lds(c) ? 1 : 0;
     a.noise_in_lds = md_noise_in_lds(c, G) ? 1 : 0;
-    a.step_at = &c.d_state->step;
+    a.step_at = at.read ? at.read : &c.d_state->step;
+    a.step_next = at.next;
+    a.last = at.last ? 1 : 0;
     return a;
 }
 
 template <class Real, int G, int BPT, bool PER, int MAXT, bool POLY>
-static hipError_t launch_md_t(const Context& c, const void* cur, int mode, int block, hipStream_t s) {
-    const MDKArgs<Real> a = md_args<Real>(c, cur, mode, G);
+static hipError_t launch_md_t(const Context& c, const void* cur, int mode, int block, const StepCount& at,
+                              hipStream_t s) {
+    const MDKArgs<Real> a = md_args<Real>(c, cur, mode, G, at);
     const size_t lds = md_lds_bytes(c, G);
     static bool attr_set = false;
     if (!attr_set) {
@@ -1631,15 +1630,11 @@ static inline int md_block(int G, int m) { return std::min(1024, (G * m + 63) / 
 
 template <int S, class Real, int G, bool POLY>
 static hipError_t launch_step_one_t(const Context& c, int cur, bool last, hipStream_t s) {
-    MDKArgs<Real> a = md_args<Real>(c, c.pops[cur], MD_COUPLED, G);
-    a.step_at = &c.d_state->step_of[cur];
+    MDKArgs<Real> a = md_args<Real>(c, c.pops[cur], MD_COUPLED, G,
+                                    {&c.d_state->step_of[cur], last ? nullptr : &c.d_state->step_of[1 - cur], last});
     a.dst = c.pops[1 - cur];
     a.now = c.marks[cur];
-    if (!last) {
-        a.next = c.marks[1 - cur];
-        a.step_next = &c.d_state->step_of[1 - cur];
-    }
-    a.last = last ? 1 : 0;
+    if (!last) a.next = c.marks[1 - cur];
     static bool attr_set = false;
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute((const void*)k_step_one<S, Real, G, POLY>,
@@ -1673,7 +1668,7 @@ hipError_t launch_step_one_g(const Context& c, int cur, bool last, hipStream_t s
 }
 
 template <class Real, bool PER, bool POLY>
-hipError_t launch_md_g(const Context& c, const void* cur, int mode, hipStream_t s) {
+hipError_t launch_md_g(const Context& c, const void* cur, int mode, const StepCount& at, hipStream_t s) {
     // G lanes per bead (the context's choice); with one lane per bead the 512-thread
     // bound up to 512 beads, the 1024-thread bound beyond, up to 4 beads per lane
     const int m = std::max(c.max_beads, 1);
@@ -1681,33 +1676,41 @@ hipError_t launch_md_g(const Context& c, const void* cur, int mode, hipStream_t 
     if (!md_lanes_valid(G, m)) return hipErrorInvalidValue;
     auto blk = [](int t) { return md_block(1, t); };
     switch (G) {
-        case 16: return launch_md_t<Real, 16, 1, PER, 512, POLY>(c, cur, mode, blk(16 * m), s);
-        case 8: return launch_md_t<Real, 8, 1, PER, 512, POLY>(c, cur, mode, blk(8 * m), s);
-        case 4: return launch_md_t<Real, 4, 1, PER, 512, POLY>(c, cur, mode, blk(4 * m), s);
+        case 16: return launch_md_t<Real, 16, 1, PER, 512, POLY>(c, cur, mode, blk(16 * m), at, s);
+        case 8: return launch_md_t<Real, 8, 1, PER, 512, POLY>(c, cur, mode, blk(8 * m), at, s);
+        case 4: return launch_md_t<Real, 4, 1, PER, 512, POLY>(c, cur, mode, blk(4 * m), at, s);
         case 2:
             // two lanes per bead: up to 256 beads in the 512-thread bound, up to 512 in the
             // 1024-thread one
-            if (2 * m <= 512) return launch_md_t<Real, 2, 1, PER, 512, POLY>(c, cur, mode, blk(2 * m), s);
-            return launch_md_t<Real, 2, 1, PER, 1024, POLY>(c, cur, mode, blk(2 * m), s);
+            if (2 * m <= 512) return launch_md_t<Real, 2, 1, PER, 512, POLY>(c, cur, mode, blk(2 * m), at, s);
+            return launch_md_t<Real, 2, 1, PER, 1024, POLY>(c, cur, mode, blk(2 * m), at, s);
         default: break;
     }
-    if (m <= 512) return launch_md_t<Real, 1, 1, PER, 512, POLY>(c, cur, mode, blk(m), s);
-    if (m <= 1024) return launch_md_t<Real, 1, 1, PER, 1024, POLY>(c, cur, mode, blk(m), s);
-    if (m <= 2048) return launch_md_t<Real, 1, 2, PER, 1024, POLY>(c, cur, mode, 1024, s);
-    if (m <= 3072) return launch_md_t<Real, 1, 3, PER, 1024, POLY>(c, cur, mode, 1024, s);
-    if (m <= 4096) return launch_md_t<Real, 1, 4, PER, 1024, POLY>(c, cur, mode, 1024, s);
+    if (m <= 512) return launch_md_t<Real, 1, 1, PER, 512, POLY>(c, cur, mode, blk(m), at, s);
+    if (m <= 1024) return launch_md_t<Real, 1, 1, PER, 1024, POLY>(c, cur, mode, blk(m), at, s);
+    if (m <= 2048) return launch_md_t<Real, 1, 2, PER, 1024, POLY>(c, cur, mode, 1024, at, s);
+    if (m <= 3072) return launch_md_t<Real, 1, 3, PER, 1024, POLY>(c, cur, mode, 1024, at, s);
+    if (m <= 4096) return launch_md_t<Real, 1, 4, PER, 1024, POLY>(c, cur, mode, 1024, at, s);
     return hipErrorInvalidValue;
 }
 
 // the eight variants are compiled as objects of their own (md_bead.hip)
-extern template hipError_t launch_md_g<float, false, false>(const Context&, const void*, int, hipStream_t);
-extern template hipError_t launch_md_g<float, true, false>(const Context&, const void*, int, hipStream_t);
-extern template hipError_t launch_md_g<float, false, true>(const Context&, const void*, int, hipStream_t);
-extern template hipError_t launch_md_g<float, true, true>(const Context&, const void*, int, hipStream_t);
-extern template hipError_t launch_md_g<double, false, false>(const Context&, const void*, int, hipStream_t);
-extern template hipError_t launch_md_g<double, true, false>(const Context&, const void*, int, hipStream_t);
-extern template hipError_t launch_md_g<double, false, true>(const Context&, const void*, int, hipStream_t);
-extern template hipError_t launch_md_g<double, true, true>(const Context&, const void*, int, hipStream_t);
+extern template hipError_t launch_md_g<float, false, false>(const Context&, const void*, int, const StepCount&,
+                                                                  hipStream_t);
+extern template hipError_t launch_md_g<float, true, false>(const Context&, const void*, int, const StepCount&,
+                                                                  hipStream_t);
+extern template hipError_t launch_md_g<float, false, true>(const Context&, const void*, int, const StepCount&,
+                                                                  hipStream_t);
+extern template hipError_t launch_md_g<float, true, true>(const Context&, const void*, int, const StepCount&,
+                                                                  hipStream_t);
+extern template hipError_t launch_md_g<double, false, false>(const Context&, const void*, int, const StepCount&,
+                                                                  hipStream_t);
+extern template hipError_t launch_md_g<double, true, false>(const Context&, const void*, int, const StepCount&,
+                                                                  hipStream_t);
+extern template hipError_t launch_md_g<double, false, true>(const Context&, const void*, int, const StepCount&,
+                                                                  hipStream_t);
+extern template hipError_t launch_md_g<double, true, true>(const Context&, const void*, int, const StepCount&,
+                                                                  hipStream_t);
 extern template hipError_t launch_step_one_g<LB_STORE_F64, false>(const Context&, int, bool, hipStream_t);
 extern template hipError_t launch_step_one_g<LB_STORE_F64, true>(const Context&, int, bool, hipStream_t);
 extern template hipError_t launch_step_one_g<LB_STORE_F32, false>(const Context&, int, bool, hipStream_t);

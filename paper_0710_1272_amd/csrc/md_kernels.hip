@@ -431,20 +431,20 @@ bool md_lanes_valid(int lanes, int max_beads) {
 }
 
 template <class Real>
-static hipError_t launch_md_r(const Context& c, const void* cur, int mode, hipStream_t s) {
+static hipError_t launch_md_r(const Context& c, const void* cur, int mode, const StepCount& at, hipStream_t s) {
     bool any_periodic = false;
     for (const Replica& R : c.reps)
         if (R.n_beads > 0 && (!R.fs[0] || !R.fs[1] || !R.fs[2])) any_periodic = true;
     if (c.md.rigid || c.md.kappa_phi != 0.0)
-        return any_periodic ? launch_md_g<Real, true, true>(c, cur, mode, s)
-                            : launch_md_g<Real, false, true>(c, cur, mode, s);
-    return any_periodic ? launch_md_g<Real, true, false>(c, cur, mode, s)
-                        : launch_md_g<Real, false, false>(c, cur, mode, s);
+        return any_periodic ? launch_md_g<Real, true, true>(c, cur, mode, at, s)
+                            : launch_md_g<Real, false, true>(c, cur, mode, at, s);
+    return any_periodic ? launch_md_g<Real, true, false>(c, cur, mode, at, s)
+                        : launch_md_g<Real, false, false>(c, cur, mode, at, s);
 }
 
-hipError_t launch_md(const Context& c, const void* cur, int mode, hipStream_t s) {
-    if (c.storage == LB_STORE_F64) return launch_md_r<double>(c, cur, mode, s);
-    return launch_md_r<float>(c, cur, mode, s);
+hipError_t launch_md(const Context& c, const void* cur, int mode, hipStream_t s, const StepCount& at) {
+    if (c.storage == LB_STORE_F64) return launch_md_r<double>(c, cur, mode, at, s);
+    return launch_md_r<float>(c, cur, mode, at, s);
 }
 
 // One lane a bead (more than 256 beads by default) stays with separate launches: the bead step then
