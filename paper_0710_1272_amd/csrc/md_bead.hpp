@@ -461,7 +461,7 @@ __device__ __forceinline__ double rcp64(double b) {
     return __builtin_fma(__builtin_fma(-b, r, 1.0), r, r);
 }
 
-// Whether any thread of the block passes need = true.  Two words, used in turn by successive
+// Whether any thread of the block (of its waves still running) passes need = true.  Two words, used in turn by successive
 // votes (stamp counts them), so that nothing has to be cleared; between two votes on one word
 // lies the barrier of the vote in between.
 __device__ __forceinline__ bool block_vote(int* words, int stamp, bool need) {
@@ -734,6 +734,14 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
         }
     }
 
+    // Rebuild vote: a wave whose beads moved too far in substep s stores ~s into word s & 1
+    // (not s + 1: merged with the loop's own increment that would make the substep number
+    // divergent in the compiler's eyes, and every decision of the loop a vector branch).
+    // Two words, so that one barrier per substep separates the writes of a substep from its
+    // reads and from the next writes to the same word; nothing has to be cleared.
+    __shared__ int vote[2], inner_vote[2], block_votes[2];
+    if (tid < 2) vote[tid] = inner_vote[tid] = block_votes[tid] = 0;
+    int votes = 0;  // votes taken with block_vote
     if (a.mode & MD_SUBSTEPS) __syncthreads();
 
     // Verlet lists: kept from the previous launch (stored with the positions they were
@@ -742,7 +750,7 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
     // (kept in a scalar: every later decision of the whole workgroup then is a scalar branch)
     bool build = __builtin_amdgcn_readfirstlane(kept == 0.0 ? 1 : 0) != 0;
     if (!build && (a.mode & MD_SUBSTEPS)) {
-        int moved = 0;
+        bool moved = false;
 #pragma unroll
         for (int k = 0; k < BPT; ++k) {
             const int gi = b0 + grp + k * NG;
@@ -754,9 +762,11 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
             }
             const Real disp2 = sum_sq((Real)(r[k][0] - rref[k][0]), (Real)(r[k][1] - rref[k][1]),
                                       (Real)(r[k][2] - rref[k][2]));
-            moved |= !(disp2 <= hs2);
+            moved = moved | !(disp2 <= hs2);
         }
-        build = __builtin_amdgcn_readfirstlane(__syncthreads_or(moved)) != 0;
+        // (a vote of the waves that take part: the library's workgroup reductions are for all
+        // threads of the workgroup, and in the one-launch step some have left)
+        build = block_vote(block_votes, votes++, moved);
         if (!build && list_lds) {
             // the kept list into LDS: what was fetched ahead, then 8 entries a lane per round trip
 #pragma unroll
@@ -851,14 +861,6 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
     // keeps the skipped terms zero under any rounding of the distance)
     const Real rcw_gate = (Real)(md.rcw + 1e-3);
     const Real fdrive = (Real)md.f_drive;
-    // Rebuild vote: a wave whose beads moved too far in substep s stores ~s into word s & 1
-    // (not s + 1: merged with the loop's own increment that would make the substep number
-    // divergent in the compiler's eyes, and every decision of the loop a vector branch).
-    // Two words, so that one barrier per substep separates the writes of a substep from its
-    // reads and from the next writes to the same word; nothing has to be cleared.
-    __shared__ int vote[2], inner_vote[2], shake_vote[2];
-    if (tid < 2) vote[tid] = inner_vote[tid] = shake_vote[tid] = 0;
-    int votes = 0;  // rigid bonds: convergence votes taken
     __syncthreads();
 
     // chain neighbours (constant over the step) and the register slots of the lists
@@ -907,7 +909,6 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
 #pragma unroll
         for (int w = 0; w < LB_MAX_WALLS; ++w) near_wall[k][w] = false;
     }
-    const int wave = tid >> 6;
 
     Real bond_max = 0;  // largest squared bond length met
     unsigned long long in_solid = 0, outside = 0;  // the wave's lanes
@@ -1280,7 +1281,7 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
                 const double B = on ? 4.0 * im * (sv[0] * dref[0] + sv[1] * dref[1] + sv[2] * dref[2]) : 1.0;
                 const double Aa = on ? -2.0 * im * (sv[0] * dm1[0] + sv[1] * dm1[1] + sv[2] * dm1[2]) : 0.0;
                 const double Cc = on ? -2.0 * im * (sv[0] * dp1[0] + sv[1] * dp1[1] + sv[2] * dp1[2]) : 0.0;
-                const bool any_bad = block_vote(shake_vote, votes++, bad);
+                const bool any_bad = block_vote(block_votes, votes++, bad);
                 if (!any_bad) break;
                 if (it >= md.shake_iter) {
                     flags |= LB_ERR_CONSTRAINT;
@@ -1555,7 +1556,7 @@ __global__ __launch_bounds__(512) void k_step_one(MDKArgs<Real> a, int bead_thre
 static inline int md_nmax(const Context& c) { return (c.max_beads + 63) / 64 * 64; }
 
 static constexpr size_t kMDLdsBudget = 150 * 1024;
-// the bead kernel's static LDS (block sums 512 B, rebuild vote 32 B) stays below this
+// the bead kernel's static LDS (block sums 512 B, the words of three votes 24 B) stays below this
 static constexpr int kMDStaticLds = 2048;
 
 static inline size_t md_base_lds(size_t nmax) { return nmax * (6 * sizeof(double) + sizeof(int) + 1); }
