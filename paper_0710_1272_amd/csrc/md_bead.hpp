@@ -1085,9 +1085,9 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
                 // entries beyond the register slots, U a lane and round: a round, not an entry,
                 // costs the two LDS round trips (entry, position)
                 constexpr int U = G == 1 ? 4 : 2;
-                const bool overflow = cnt[k] > kNeighbourMax;
-                const int lim = own[k] ? (overflow ? n : cin[k]) : 0;
-                for (int q0 = overflow ? gl : gl + K * G; q0 < lim; q0 += U * G) {
+                const bool overflow = own[k] && cnt[k] > kNeighbourMax;
+                const int lim = own[k] && !overflow ? cin[k] : 0;
+                for (int q0 = gl + K * G; q0 < lim; q0 += U * G) {
                     int j[U];
                     bool ok[U];
                     double pq[U][3];
@@ -1095,17 +1095,22 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
                     for (int t = 0; t < U; ++t) {
                         const int q = q0 + t * G;
                         ok[t] = q < lim;
-                        j[t] = !ok[t] ? i : overflow ? q : entry_at(q, i, k);
+                        j[t] = ok[t] ? entry_at(q, i, k) : i;
                     }
 #pragma unroll
-                    for (int t = 0; t < U; ++t) {
+                    for (int t = 0; t < U; ++t)
 #pragma unroll
                         for (int c = 0; c < 3; ++c) pq[t][c] = PB[3 * j[t] + c];
-                        if (overflow)
-                            ok[t] = ok[t] && !(j[t] == i || (j[t] == i + 1 && bnk[k]) || (j[t] == i - 1 && bpk[k]));
-                    }
 #pragma unroll
                     for (int t = 0; t < U; ++t) pair(pq[t], ok[t]);
+                }
+                // A list that overflowed: all beads, one after the other.  Among them are beads whose
+                // position is not finite, which no list holds: only a pair within the cutoff is added.
+                for (int q = gl; q < (overflow ? n : 0); q += G) {
+                    if (q == i || (q == i + 1 && bnk[k]) || (q == i - 1 && bpk[k])) continue;
+                    const double pq[3] = {PB[3 * q], PB[3 * q + 1], PB[3 * q + 2]};
+                    Real d[3];
+                    if (separation_v<Real, PERIODIC>(r[k], pq, per, nd, d) < rc2) pair(pq, true);
                 }
             }
             F[k][0] = group_sum<G>(fx);
