@@ -117,8 +117,8 @@ __device__ __forceinline__ Geom load_geom(const Replica& R) {
 // A wall's slab X0..X1 and pore prism Y0..Y1 x Z0..Z1 (solid node cubes span [i - 1/2, i + 1/2]).
 // Its pore nodes are those with lo[a] <= floor(r + 1/2) <= hi on every axis, or lo[a] <= t < hi1[a]
 // for t = r + 1/2; on a free-slip axis the node index is clamped into the box, so that a bound on a
-// face of the box holds for every t (of a bead less than 2^31 nodes away).  A wall without a pore
-// has bounds that nothing meets.
+// face of the box holds for every t (of a bead less than kNowhere away).  A wall without a pore has
+// bounds that nothing meets.
 struct WallBounds {
     double x0, x1, y0, y1, z0, z1;
     double lo[3], hi1[3];
@@ -141,9 +141,21 @@ __device__ __forceinline__ WallBounds wall_bounds(const WallInts& I) {
             {(double)I.lo[0], (double)I.lo[1], (double)I.lo[2]}, {(double)I.hi1[0], (double)I.hi1[1], (double)I.hi1[2]}};
 }
 
-// Whether the nearest node floor(r + 1/2) of r is a node of wall w's pore; a periodic axis wraps
-// the index as the node lookup does.
+// A bead that is nowhere: a coordinate is not finite or, on a free-slip axis, absurdly far out.  The
+// branch-free wall terms below hold for all others.
+constexpr double kNowhere = 1e9;
 template <bool PERIODIC>
+__device__ __forceinline__ bool is_nowhere(const Geom& G, const double* r) {
+    bool out = false;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) out = out | !(fabs(r[a]) < (PERIODIC && !G.fs[a] ? HUGE_VAL : kNowhere));
+    return out;
+}
+
+// Whether the nearest node floor(r + 1/2) of r is a node of wall w's pore; a periodic axis wraps
+// the index as the node lookup does.  NOWHERE: r may be nowhere; a bound on a free-slip face of the
+// box holds for it as for any other (the lookup clamps the index into the box).
+template <bool PERIODIC, bool NOWHERE = false>
 __device__ __forceinline__ bool wall_pore_node(const Geom& G, const WallBounds& B, const int* w, const double* r) {
     if (PERIODIC && !pore_open(w)) return false;
     bool in = true;
@@ -157,7 +169,12 @@ __device__ __forceinline__ bool wall_pore_node(const Geom& G, const WallBounds& 
             if (k < 0) k += G.n[a];
             in = in && k >= w[2 * a] && k <= w[2 * a + 1];
         } else {
-            in = in & (t >= B.lo[a]) & (t < B.hi1[a]);
+            bool lo = t >= B.lo[a], hi = t < B.hi1[a];
+            if constexpr (NOWHERE) {
+                lo = lo | (w[2 * a] <= 0);
+                hi = hi | (w[2 * a + 1] >= G.n[a] - 1);
+            }
+            in = in & lo & hi;
         }
     }
     return in;
@@ -192,6 +209,34 @@ __device__ __forceinline__ double wall_dist2(const Geom& G, const WallBounds& B,
     dv[1] = dy;
     dv[2] = dz;
     return sum_sq(dx, dy, dz);
+}
+
+// The nearest solid surface over the walls (squared distance and vector, as wall_dist2) and whether
+// the nearest node is a pore node, for a bead that is nowhere; other beads keep what they have.  It is
+// at a wall only if its x is within reach, is in no pore's cross-section, and of its place there only
+// the slab's distance counts.
+template <bool PERIODIC>
+__device__ __forceinline__ void walls_of_nowhere(const Geom& G, const double* r, double xw, double reach,
+                                                 double* best2, double* dvw, bool* pore) {
+    if (!is_nowhere<PERIODIC>(G, r)) return;
+    *best2 = HUGE_VAL;
+    dvw[0] = dvw[1] = dvw[2] = 0.0;
+    *pore = false;
+#pragma unroll
+    for (int w = 0; w < LB_MAX_WALLS; ++w) {
+        if (w >= G.n_walls) break;
+        int wl[6];  // (nothing of this rare path is to be held through the substep loop)
+#pragma unroll
+        for (int m = 0; m < 6; ++m) wl[m] = here(G.wall[w][m]);
+        const WallBounds B = wall_bounds(wall_ints(G, wl));
+        if (!(xw > B.x0 - reach && xw < B.x1 + reach)) continue;
+        const double dx = xw - fmin(fmax(xw, B.x0), B.x1);
+        if (dx * dx < *best2) {
+            *best2 = dx * dx;
+            dvw[0] = dx;
+        }
+        *pore = *pore || (pore_open(wl) && wall_pore_node<PERIODIC, true>(G, B, wl, r));
+    }
 }
 
 // 1/x: the hardware reciprocal in FP32 (about 1 ulp), an exact division in FP64
@@ -887,7 +932,10 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
     // cannot have left the box.
     const bool x_periodic = PERIODIC && !GM.fs[0];
     const double zone = md.zone;
-    bool near_wall[BPT][LB_MAX_WALLS], near_face[BPT];  // of any bead of the wave
+    // What any bead of the wave is near, in one scalar: bit w of wall w, kFace of a face, and kLost if
+    // one of the beads at a wall is nowhere (a bead that gets there forces a build).
+    constexpr unsigned kWalls = (1u << LB_MAX_WALLS) - 1u, kFace = 1u << LB_MAX_WALLS, kLost = 2u << LB_MAX_WALLS;
+    unsigned near[BPT];
     bool more[BPT];  // whether any bead of the wave has list entries beyond the register slots
     int cin[BPT];    // entries the substeps go through: of the inner list, or of the Verlet list
     bool half[BPT];  // inner list: whether any bead of the wave has entries in the slots' upper half
@@ -906,8 +954,7 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
         const int i = own[k] ? grp + k * NG : 0;
         prev3[k] = 3 * (bpk[k] ? i - 1 : i);
         next3[k] = 3 * (bnk[k] ? i + 1 : i);
-#pragma unroll
-        for (int w = 0; w < LB_MAX_WALLS; ++w) near_wall[k][w] = false;
+        near[k] = 0;
     }
 
     Real bond_max = 0;  // largest squared bond length met
@@ -960,16 +1007,19 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
                 const int i = grp + k * NG;
                 const double xw = x_periodic ? r[k][0] - nd[0] * floor((r[k][0] + 0.5) / nd[0]) : r[k][0];
                 bool f_near = false;
+                unsigned m = 0;
 #pragma unroll
                 for (int w = 0; w < LB_MAX_WALLS; ++w) {
                     if (w >= GM.n_walls) break;
-                    near_wall[k][w] = __ballot(own[k] && xw > GM.wall[w][0] - 0.5 - zone &&
-                                               xw < GM.wall[w][1] + 0.5 + zone) != 0ull;
+                    if (__ballot(own[k] && xw > GM.wall[w][0] - 0.5 - zone && xw < GM.wall[w][1] + 0.5 + zone) != 0ull)
+                        m |= 1u << w;
                 }
+                if (m != 0u && __ballot(own[k] && is_nowhere<PERIODIC>(GM, r[k])) != 0ull) m |= kLost;
 #pragma unroll
                 for (int c = 0; c < 3; ++c)
                     if (GM.fs[c]) f_near = f_near || !(r[k][c] + 0.5 >= zone && (nn[c] - 0.5) - r[k][c] >= zone);
-                near_face[k] = __ballot(own[k] && f_near) != 0ull;
+                if (__ballot(own[k] && f_near) != 0ull) m |= kFace;
+                near[k] = __builtin_amdgcn_readfirstlane(m);
                 cin[k] = cnt[k];
                 if constexpr (INNER) {
 #pragma unroll
@@ -1159,13 +1209,13 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
             // nearest solid surface over the walls (min, earlier wall on ties) and the pore
             // drive (a bead whose nearest node is a pore node lies within half a node of its
             // wall's slab, so inside the zone); beyond the zone both are zero
-            if (near_wall[k][0] || near_wall[k][1]) {
+            if (near[k] & kWalls) {
                 const double xw = x_periodic ? r[k][0] - nd[0] * floor((r[k][0] + 0.5) / nd[0]) : r[k][0];
                 double best2 = HUGE_VAL, dvw[3] = {0.0, 0.0, 0.0};
                 bool pore = false;
 #pragma unroll
                 for (int w = 0; w < LB_MAX_WALLS; ++w) {
-                    if (!near_wall[k][w]) continue;
+                    if (!(near[k] >> w & 1u)) continue;
                     double dv[3];
                     // (held through a polymer model's loop, the bounds would push its constraint
                     // solve out of the registers)
@@ -1183,6 +1233,8 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
                     for (int c = 0; c < 3; ++c) dvw[c] = closer ? dv[c] : dvw[c];
                     pore = pore | wall_pore_node<PERIODIC>(GM, B, GM.wall[w], r[k]);
                 }
+                if (__builtin_expect((near[k] & kLost) != 0u, 0))
+                    walls_of_nowhere<PERIODIC>(GM, r[k], xw, md.rcw, &best2, dvw, &pore);
                 in_solid |= __ballot(own[k] & (best2 == 0.0));
                 const bool hit = (best2 < (double)rcw2) & (best2 > 0.0);
                 const Real c = wca_coef<Real>(hit ? (Real)best2 : rcw2, epsw, sigw2, rcw2);
@@ -1191,7 +1243,7 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
                 F[k][0] += pore ? fdrive : Real(0);
             }
             // free-slip faces at -1/2 and n - 1/2 (the WCA terms only within the cutoff)
-            if (near_face[k]) {
+            if (near[k] & kFace) {
                 // (without PERIODIC every axis has faces)
                 Real dlo[3], dhi[3], least = rcw_gate;
 #pragma unroll

@@ -129,7 +129,8 @@ __global__ __launch_bounds__(256) void k_observe(const Replica* __restrict__ rep
 #pragma unroll
         for (int w = 0; w < LB_MAX_WALLS; ++w) {
             if (w >= GM.n_walls) break;
-            pore = pore || wall_pore_node<true>(GM, wall_bounds(wall_ints(GM, GM.wall[w])), GM.wall[w], r);
+            pore = pore || (pore_open(GM.wall[w]) &&
+                            wall_pore_node<true, true>(GM, wall_bounds(wall_ints(GM, GM.wall[w])), GM.wall[w], r));
         }
         const bool tr = r[0] > xmid;
         o[0] += tr ? 1.0 : 0.0;
