@@ -157,6 +157,8 @@ typedef struct lbmd_config {
     int storage;                       /* LB_STORE_* for every replica */
     lbmd_md_params md;
     const lbmd_initial_state* init;    /* may be NULL: rest fluid at rho0, no beads allowed */
+    /* the lattice kernel's launch shape; naming any of the three keeps coupled steps in launches
+     * of their own (lb_one_launch), so that the shape is theirs too */
     int block_size;                    /* threads per block of the lattice kernel, 0 = default */
     int lattice_mapping;               /* LB_MAP_*: how lattice-kernel threads map to nodes */
     int xcd_order;                     /* LB_XCD_* or a chunk size > 0: tile order over the 8 XCDs */
@@ -335,10 +337,18 @@ int lb_conserved_noalloc(const void* pops, int storage, const lbmd_replica* rep,
  * non-positive box size. */
 long long lb_plane_stride(const lbmd_replica* rep, int storage);
 
-/* Lattice-kernel launch shape in use (threads per block). */
+/* Whether a coupled step runs in one launch (1; one box of moderate size with nearest-node coupling,
+ * free-slip faces, no thermal source, no observable record, more than one lane a bead and no launch
+ * shape named in lbmd_config) or as a lattice sweep beside the bead kernel with the spread behind
+ * them (0).  Results are the same.  In one launch the sweep has a shape of its own: 512 threads, flat,
+ * contiguous per XCD, ordinary stores.  LB_EINVAL for a NULL context. */
+int lb_one_launch(const lbmd_ctx* ctx);
+
+/* Lattice-kernel launch shape in use (threads per block); of lattice-only steps and of coupled steps
+ * in launches of their own. */
 int lb_block_size(const lbmd_ctx* ctx);
 
-/* Lattice-kernel launch shape in use: threads per block, LB_MAP_FLAT/ROWS/SHIFTED/FLAT2, the XCD
+/* That launch shape whole: threads per block, LB_MAP_FLAT/ROWS/SHIFTED/FLAT2, the XCD
  * tile order (LB_XCD_HARDWARE, LB_XCD_CONTIGUOUS or a chunk size) and whether the
  * populations are written with non-temporal stores (1: both buffers together exceed
  * 340 MB, so they are streamed past the last-level cache; 0: they stay cached between

@@ -151,8 +151,10 @@ Replica make_replica(const lbmd_replica& in, size_t elem) {
     return R;
 }
 
-// one box with beads, nearest-node coupling, free-slip faces and no thermal source
+// one box with beads, nearest-node coupling, free-slip faces and no thermal source, and no lattice
+// launch shape asked for (the one-launch step has its own)
 int mark_chunks(const lbmd_config* cfg) {
+    if (cfg->block_size != 0 || cfg->lattice_mapping != LB_MAP_AUTO || cfg->xcd_order != LB_XCD_AUTO) return 0;
     if (cfg->n_replicas != 1 || cfg->md.stencil != LB_STENCIL_NGP) return 0;
     const lbmd_replica& R = cfg->replicas[0];
     const long long V = (long long)R.nx * R.ny * R.nz;
@@ -1118,6 +1120,11 @@ int lb_pattern_copy(lbmd_ctx* ctx, int alternate) {
     HIP_TRY(launch_pattern(c, c.pops[c.cur], c.pops[1 - c.cur], c.stream));
     if (alternate) c.cur = 1 - c.cur;
     return LB_OK;
+}
+
+int lb_one_launch(const lbmd_ctx* ctx) {
+    if (!ctx) return fail(LB_EINVAL, "ctx is NULL");
+    return step_one_fits(ctx->c) ? 1 : 0;
 }
 
 int lb_md_lanes(const lbmd_ctx* ctx) {

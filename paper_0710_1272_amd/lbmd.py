@@ -36,7 +36,7 @@ LB_ERR_CONSTRAINT = 32
 LB_STENCIL_NGP, LB_STENCIL_TRILINEAR = 0, 1
 
 EXPORTED = ["lb_required_bytes", "lb_validate_config", "lb_init", "lb_step", "lb_graph_prepare", "lb_couple", "md_step",
-            "lb_moments", "lb_moments_bytes", "lb_moments_range", "lb_block_size", "lb_launch_shape", "lb_md_lanes", "lb_destroy",
+            "lb_moments", "lb_moments_bytes", "lb_moments_range", "lb_block_size", "lb_launch_shape", "lb_one_launch", "lb_md_lanes", "lb_destroy",
             "lb_strerror", "lb_last_error_message", "lb_conserved_noalloc", "lb_pattern_copy", "lb_plane_stride"]
 
 
@@ -114,6 +114,7 @@ def lib():
         L.lb_launch_shape.argtypes = [C.c_void_p, C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int),
                                       C.POINTER(C.c_int)]
         L.lb_md_lanes.argtypes = [C.c_void_p]
+        L.lb_one_launch.argtypes = [C.c_void_p]
         L.lb_pattern_copy.argtypes = [C.c_void_p, C.c_int]
         L.lb_conserved_noalloc.argtypes = [C.c_void_p, C.c_int, C.POINTER(lbmd_replica), C.c_void_p, C.c_void_p]
         L.lb_plane_stride.argtypes = [C.POINTER(lbmd_replica), C.c_int]
@@ -280,6 +281,14 @@ class Simulation:
         names = {LB_MAP_FLAT: "flat", LB_MAP_ROWS: "rows", LB_MAP_SHIFTED: "shifted", LB_MAP_FLAT2: "flat2"}
         return {"block": b.value, "mapping": names[m.value],
                 "xcd_order": x.value, "nt_stores": bool(nt.value), "md_lanes": self.md_lanes}
+
+    @property
+    def one_launch(self) -> bool:
+        """Whether a coupled step runs in one launch."""
+        v = lib().lb_one_launch(self.ctx)
+        if v < 0:
+            _check(v, "lb_one_launch")
+        return bool(v)
 
     def pattern_copy(self, alternate: bool = False):
         """One same-pattern reference launch of the lattice kernel (lb_pattern_copy); with
