@@ -132,8 +132,9 @@ typedef struct lbmd_initial_state {
 
 #define LB_CFG_NO_GRAPH 1u   /* enqueue plain launches instead of captured HIP graphs */
 #define LB_CFG_AUTOTUNE 2u   /* time candidate launch shapes (lattice kernel, lanes per bead of
-                                the bead kernel) at lb_init and keep the fastest; the bead
-                                state is restored after the trial steps */
+                                the bead kernel, coupled steps in one launch or several) at
+                                lb_init and keep the fastest; the state is restored after the
+                                trial steps */
 #define LB_CFG_DETERMINISTIC 4u /* bitwise identical results from run to run for one configuration.
                                    The nearest-node path always is: one leader bead per node adds
                                    the summed reaction of the node's beads in bead order.  With it,
@@ -143,7 +144,8 @@ typedef struct lbmd_initial_state {
                                    and adds each node's sums to its populations once, instead of
                                    floating-point atomic adds whose order varies; and LB_CFG_AUTOTUNE
                                    leaves the lanes per bead at their choice by bead count, since
-                                   they set the order of the bead-force sums.  The lattice kernel's
+                                   they set the order of the bead-force sums, and with them the
+                                   launches of a coupled step.  The lattice kernel's
                                    launch shape never changes results.  A contribution above 512
                                    in magnitude is dropped and sets LB_ERR_NONFINITE (so that no
                                    node's 64-bit sum can overflow below 64 contributions).  FP16 and

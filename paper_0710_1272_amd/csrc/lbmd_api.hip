@@ -735,6 +735,86 @@ hipError_t enqueue_step(Context& c, int mode, int cur, int k, int len, hipStream
     return launch_stream_collide(c, src, dst, true, main);
 }
 
+int build_graph(Context& c, int mode, int parity, int len, hipGraphExec_t* out);
+
+// Coupled steps in one launch or in launches of their own: times graphs of 16 steps, as lb_step
+// launches them, of the separate launches with the lanes a bead found beside the sweep, and of the
+// one launch with every lane count it holds (or the caller's); each from the same state, which is put
+// back afterwards: the populations, the bead buffer and the run state.  The marks of the trial steps
+// are cleared, since the steps that follow bear the same numbers.
+int autotune_route(Context& c, int given_lanes) {
+    if (!c.marks[0].stamp || c.obs_every > 0) return LB_OK;
+    struct Route {
+        bool one;
+        int lanes;
+    };
+    std::vector<Route> routes{{false, c.md_lanes}};
+    for (int G : {2, 4, 8, 16})
+        if ((given_lanes == 0 || given_lanes == G) && md_lanes_valid(G, c.max_beads) && step_one_lanes(G, c.max_beads))
+            routes.push_back({true, G});
+    if (routes.size() < 2) return LB_OK;
+    const size_t real = c.storage == LB_STORE_F64 ? sizeof(double) : sizeof(float);
+    const size_t bead_bytes = bead_layout(c.ntot_beads, (int)c.reps.size(), real, 0, false).total;
+    const size_t pop_bytes = align256((size_t)c.pop_elems * store_size(c.storage));
+    char* save = nullptr;
+    HIP_TRY(hipMalloc((void**)&save, pop_bytes + bead_bytes + sizeof(RunState)));
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    hipGraphExec_t g = nullptr;
+    auto copy = [&](void* dst, const void* src, size_t n) {
+        return hipMemcpyAsync(dst, src, n, hipMemcpyDeviceToDevice, c.stream);
+    };
+    auto put_back = [&]() -> hipError_t {
+        hipError_t e;
+        if ((e = copy(c.pops[c.cur], save, pop_bytes)) != hipSuccess) return e;
+        if ((e = copy(c.beads, save + pop_bytes, bead_bytes)) != hipSuccess) return e;
+        if ((e = copy(c.d_state, save + pop_bytes + bead_bytes, sizeof(RunState))) != hipSuccess) return e;
+        return hipMemsetAsync(c.marks[0].stamp, 0, c.marks_bytes, c.stream);
+    };
+    auto body = [&]() -> int {
+        HIP_TRY(hipEventCreate(&e0));
+        HIP_TRY(hipEventCreate(&e1));
+        HIP_TRY(copy(save, c.pops[c.cur], pop_bytes));
+        HIP_TRY(copy(save + pop_bytes, c.beads, bead_bytes));
+        HIP_TRY(copy(save + pop_bytes + bead_bytes, c.d_state, sizeof(RunState)));
+        Route best = routes[0];
+        float best_ms = 1e30f;
+        for (const Route& r : routes) {
+            c.one_launch = r.one;
+            c.md_lanes = r.lanes;
+            const int rc = build_graph(c, STEP_COUPLED, c.cur, Context::kGraphSteps, &g);
+            if (rc) return rc;
+            float ms = 1e30f;
+            for (int round = 0; round < 4; ++round) {  // the first one warms up
+                HIP_TRY(put_back());
+                HIP_TRY(hipEventRecord(e0, c.stream));
+                HIP_TRY(hipGraphLaunch(g, c.stream));
+                HIP_TRY(hipEventRecord(e1, c.stream));
+                HIP_TRY(hipEventSynchronize(e1));
+                float t = 0;
+                HIP_TRY(hipEventElapsedTime(&t, e0, e1));
+                if (round > 0) ms = std::min(ms, t);
+            }
+            HIP_TRY(hipGraphExecDestroy(g));
+            g = nullptr;
+            if (ms < best_ms) {
+                best_ms = ms;
+                best = r;
+            }
+        }
+        c.one_launch = best.one;
+        c.md_lanes = best.lanes;
+        HIP_TRY(put_back());
+        HIP_TRY(hipStreamSynchronize(c.stream));
+        return LB_OK;
+    };
+    const int rc = body();
+    if (g) (void)hipGraphExecDestroy(g);
+    if (e0) (void)hipEventDestroy(e0);
+    if (e1) (void)hipEventDestroy(e1);
+    (void)hipFree(save);
+    return rc;
+}
+
 int build_graph(Context& c, int mode, int parity, int len, hipGraphExec_t* out) {
     hipGraph_t g = nullptr;
     // the caller's stream may be the null stream, which cannot be captured: capture on
@@ -893,6 +973,7 @@ int lb_init(const lbmd_config* cfg, const lbmd_buffers* bufs, void* hip_stream, 
             c.marks[k].stamp = (long long*)(wb + W.stamps) + (size_t)k * W.chunks;
             c.marks[k].mask = (unsigned long long*)(wb + W.masks) + (size_t)k * W.chunks;
         }
+    c.marks_bytes = W.chunks > 0 ? W.total - W.stamps : 0;
 
     auto check = [&](hipError_t e, const char* what) -> int {
         if (e == hipSuccess) return LB_OK;
@@ -900,7 +981,7 @@ int lb_init(const lbmd_config* cfg, const lbmd_buffers* bufs, void* hip_stream, 
     };
     if ((rc = check(hipMemcpy(c.d_reps, c.reps.data(), sizeof(Replica) * c.reps.size(), hipMemcpyHostToDevice), "upload replicas")))
         return bail(rc);
-    if (W.chunks > 0 && (rc = check(hipMemset(wb + W.stamps, 0, W.total - W.stamps), "clear marks"))) return bail(rc);
+    if (c.marks_bytes > 0 && (rc = check(hipMemset(c.marks[0].stamp, 0, c.marks_bytes), "clear marks"))) return bail(rc);
     RunState st{};
     st.step = cfg->init ? cfg->init->step0 : 0;
     c.host_step = st.step;
@@ -988,6 +1069,7 @@ int lb_init(const lbmd_config* cfg, const lbmd_buffers* bufs, void* hip_stream, 
         // the lanes per bead set the order of the bead-force sums: a deterministic context
         // keeps the choice by bead count (or the configured one) rather than a timed one
         if (!c.deterministic && (rc = autotune_md(c))) return bail(rc);
+        if (!c.deterministic && (rc = autotune_route(c, cfg->md_lanes))) return bail(rc);
     }
     if ((rc = check(hipStreamSynchronize(c.stream), "sync"))) return bail(rc);
     *out = ctx;

@@ -91,6 +91,8 @@ struct Context {
     std::vector<LatticeLaunch> lat_all;
     int md_lanes = 0;                  // lanes per bead of the bead kernel (0: by bead count)
     Marks marks[2] = {};               // nodes the bead kernel updates itself, by buffer parity (null: none)
+    size_t marks_bytes = 0;            // of both, from marks[0].stamp on
+    bool one_launch = true;            // coupled steps in one launch where that is possible (false: timed slower)
 
     bool use_graph = true;
     bool deterministic = false;        // LB_CFG_DETERMINISTIC
@@ -157,6 +159,8 @@ hipError_t launch_md(const Context& c, const void* cur, int mode, hipStream_t s,
 // it marks that step's nodes and takes the step number.
 hipError_t launch_mark(const Context& c, int cur, hipStream_t s);
 bool step_one_fits(const Context& c);
+// whether it holds that many lanes a bead
+bool step_one_lanes(int lanes, int max_beads);
 hipError_t launch_step_one(const Context& c, int cur, bool last, hipStream_t s);
 hipError_t launch_spread(const Context& c, void* dst, bool bump_step, hipStream_t s);
 hipError_t launch_bump(const Context& c, hipStream_t s);

@@ -453,11 +453,11 @@ hipError_t launch_md(const Context& c, const void* cur, int mode, hipStream_t s,
 // step in one launch, 83.8 apart; 200 beads, two lanes each: 54.6 and 59.2; 100 beads in 128x64x64:
 // 40.0 and 45.3, rigid 66.5 and 74.4; 12 beads in 48x24x24: 30.3 and 36.8).
 bool step_one_fits(const Context& c) {
-    if (!c.marks[0].stamp || c.obs_every > 0) return false;
-    const int m = std::max(c.max_beads, 1);
-    const int G = c.md_lanes > 0 ? c.md_lanes : md_default_lanes(m);
-    return G > 1 && md_block(G, m) <= 512;
+    if (!c.one_launch || !c.marks[0].stamp || c.obs_every > 0) return false;
+    return step_one_lanes(c.md_lanes > 0 ? c.md_lanes : md_default_lanes(c.max_beads), c.max_beads);
 }
+
+bool step_one_lanes(int lanes, int max_beads) { return lanes > 1 && md_block(lanes, std::max(max_beads, 1)) <= 512; }
 
 hipError_t launch_step_one(const Context& c, int cur, bool last, hipStream_t s) {
     const bool poly = c.md.rigid || c.md.kappa_phi != 0.0;
