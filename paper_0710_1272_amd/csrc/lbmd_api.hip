@@ -1063,6 +1063,7 @@ int lb_init(const lbmd_config* cfg, const lbmd_buffers* bufs, void* hip_stream, 
         // a mode-0 launch of the bead kernel changes nothing; it sets the kernel's
         // LDS attribute here rather than inside a later graph capture
         if ((rc = check(launch_md(c, c.pops[c.cur], 0, c.stream), "bead kernel warm-up"))) return bail(rc);
+        if (c.marks[0].stamp && (rc = check(prepare_step_one(c), "one-launch step"))) return bail(rc);
     }
     if (cfg->flags & LB_CFG_AUTOTUNE) {
         if ((rc = autotune(c))) return bail(rc);

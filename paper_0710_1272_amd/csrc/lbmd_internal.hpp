@@ -161,6 +161,7 @@ hipError_t launch_mark(const Context& c, int cur, hipStream_t s);
 bool step_one_fits(const Context& c);
 // whether it holds that many lanes a bead
 bool step_one_lanes(int lanes, int max_beads);
+hipError_t prepare_step_one(const Context& c);  // once per context and device, before the first launch
 hipError_t launch_step_one(const Context& c, int cur, bool last, hipStream_t s);
 hipError_t launch_spread(const Context& c, void* dst, bool bump_step, hipStream_t s);
 hipError_t launch_bump(const Context& c, hipStream_t s);

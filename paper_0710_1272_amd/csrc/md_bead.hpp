@@ -1686,6 +1686,24 @@ static hipError_t launch_md_t(const Context& c, const void* cur, int mode, int b
 // threads of a workgroup of G lanes a bead for m beads
 static inline int md_block(int G, int m) { return std::min(1024, (G * m + 63) / 64 * 64); }
 
+// The kernel's LDS attribute, on the current device: lb_init sets it, so that no later call has to,
+// least of all one inside a graph capture.
+template <int S, class Real, int G, bool POLY>
+static hipError_t prepare_step_one_t() {
+    return hipFuncSetAttribute((const void*)k_step_one<S, Real, G, POLY>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               160 * 1024 - kMDStaticLds);
+}
+
+template <int S, bool POLY>
+hipError_t prepare_step_one_g() {
+    using Real = typename MDReal<S>::type;
+    hipError_t e = prepare_step_one_t<S, Real, 16, POLY>();
+    if (e == hipSuccess) e = prepare_step_one_t<S, Real, 8, POLY>();
+    if (e == hipSuccess) e = prepare_step_one_t<S, Real, 4, POLY>();
+    if (e == hipSuccess) e = prepare_step_one_t<S, Real, 2, POLY>();
+    return e;
+}
+
 template <int S, class Real, int G, bool POLY>
 static hipError_t launch_step_one_t(const Context& c, int cur, bool last, hipStream_t s) {
     MDKArgs<Real> a = md_args<Real>(c, c.pops[cur], MD_COUPLED, G,
@@ -1693,13 +1711,6 @@ static hipError_t launch_step_one_t(const Context& c, int cur, bool last, hipStr
     a.dst = c.pops[1 - cur];
     a.now = c.marks[cur];
     if (!last) a.next = c.marks[1 - cur];
-    static bool attr_set = false;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void*)k_step_one<S, Real, G, POLY>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - kMDStaticLds);
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
     // 512 threads whatever the beads need: the kernel's registers leave a compute unit two waves a
     // SIMD, and a block of fewer waves than those eight would leave some of them unused
     const int tiles = (c.reps[0].V + 511) / 512;
@@ -1770,12 +1781,20 @@ extern template hipError_t launch_md_g<double, false, true>(const Context&, cons
 extern template hipError_t launch_md_g<double, true, true>(const Context&, const void*, int, const StepCount&,
                                                                   hipStream_t);
 extern template hipError_t launch_step_one_g<LB_STORE_F64, false>(const Context&, int, bool, hipStream_t);
+extern template hipError_t prepare_step_one_g<LB_STORE_F64, false>();
 extern template hipError_t launch_step_one_g<LB_STORE_F64, true>(const Context&, int, bool, hipStream_t);
+extern template hipError_t prepare_step_one_g<LB_STORE_F64, true>();
 extern template hipError_t launch_step_one_g<LB_STORE_F32, false>(const Context&, int, bool, hipStream_t);
+extern template hipError_t prepare_step_one_g<LB_STORE_F32, false>();
 extern template hipError_t launch_step_one_g<LB_STORE_F32, true>(const Context&, int, bool, hipStream_t);
+extern template hipError_t prepare_step_one_g<LB_STORE_F32, true>();
 extern template hipError_t launch_step_one_g<LB_STORE_F16DEV, false>(const Context&, int, bool, hipStream_t);
+extern template hipError_t prepare_step_one_g<LB_STORE_F16DEV, false>();
 extern template hipError_t launch_step_one_g<LB_STORE_F16DEV, true>(const Context&, int, bool, hipStream_t);
+extern template hipError_t prepare_step_one_g<LB_STORE_F16DEV, true>();
 extern template hipError_t launch_step_one_g<LB_STORE_BF16DEV, false>(const Context&, int, bool, hipStream_t);
+extern template hipError_t prepare_step_one_g<LB_STORE_BF16DEV, false>();
 extern template hipError_t launch_step_one_g<LB_STORE_BF16DEV, true>(const Context&, int, bool, hipStream_t);
+extern template hipError_t prepare_step_one_g<LB_STORE_BF16DEV, true>();
 
 }  // namespace lbmd

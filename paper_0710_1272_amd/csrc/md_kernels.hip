@@ -459,6 +459,19 @@ bool step_one_fits(const Context& c) {
 
 bool step_one_lanes(int lanes, int max_beads) { return lanes > 1 && md_block(lanes, std::max(max_beads, 1)) <= 512; }
 
+hipError_t prepare_step_one(const Context& c) {
+    const bool poly = c.md.rigid || c.md.kappa_phi != 0.0;
+    switch (c.storage) {
+        case LB_STORE_F64: return poly ? prepare_step_one_g<LB_STORE_F64, true>() : prepare_step_one_g<LB_STORE_F64, false>();
+        case LB_STORE_F32: return poly ? prepare_step_one_g<LB_STORE_F32, true>() : prepare_step_one_g<LB_STORE_F32, false>();
+        case LB_STORE_F16DEV:
+            return poly ? prepare_step_one_g<LB_STORE_F16DEV, true>() : prepare_step_one_g<LB_STORE_F16DEV, false>();
+        case LB_STORE_BF16DEV:
+            return poly ? prepare_step_one_g<LB_STORE_BF16DEV, true>() : prepare_step_one_g<LB_STORE_BF16DEV, false>();
+        default: return hipErrorNotSupported;
+    }
+}
+
 hipError_t launch_step_one(const Context& c, int cur, bool last, hipStream_t s) {
     const bool poly = c.md.rigid || c.md.kappa_phi != 0.0;
     switch (c.storage) {

@@ -7,5 +7,6 @@
 #endif
 
 namespace lbmd {
+template hipError_t prepare_step_one_g<MD_STORAGE, MD_POLY != 0>();
 template hipError_t launch_step_one_g<MD_STORAGE, MD_POLY != 0>(const Context&, int, bool, hipStream_t);
 }  // namespace lbmd

@@ -13,3 +13,11 @@ def test_no_workgroup_library_reduction_in_the_bead_step():
     with open(os.path.join(CSRC, "md_bead.hpp")) as fh:
         code = re.sub(r"//[^\n]*", "", fh.read())
     assert not re.findall(r"__syncthreads_(?:or|and|count)\b", code)
+
+
+def test_one_launch_step_sets_no_attribute_when_it_launches():
+    """The launch may fall inside a graph capture: lb_init sets the kernel's LDS attribute."""
+    with open(os.path.join(CSRC, "md_bead.hpp")) as fh:
+        code = fh.read()
+    launch = code[code.index("launch_step_one_t("):code.index("launch_step_one_g(")]
+    assert "hipLaunchKernelGGL" in launch and "hipFuncSetAttribute" not in launch
