@@ -353,8 +353,9 @@ int lb_block_size(const lbmd_ctx* ctx);
 /* That launch shape whole: threads per block, LB_MAP_FLAT/ROWS/SHIFTED/FLAT2, the XCD
  * tile order (LB_XCD_HARDWARE, LB_XCD_CONTIGUOUS or a chunk size) and whether the
  * populations are written with non-temporal stores (1: both buffers together exceed
- * 340 MB, so they are streamed past the last-level cache; 0: they stay cached between
- * steps).  Any pointer may be NULL.  Returns LB_OK or LB_EINVAL for a NULL context. */
+ * 340 MB, with 8 or more replicas 256 MB, so they are streamed past the last-level cache; 0: they
+ * stay cached between steps).  Any pointer may be NULL.  Returns LB_OK or LB_EINVAL for a NULL
+ * context. */
 int lb_launch_shape(const lbmd_ctx* ctx, int* block, int* mapping, int* xcd_order, int* nt_stores);
 
 /* Measurement reference for the lattice kernel (the streaming of Eq. lbe without the collision):

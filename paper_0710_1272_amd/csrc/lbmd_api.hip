@@ -72,6 +72,7 @@ size_t real_size(int storage) { return storage == LB_STORE_F64 ? 8 : 4; }
 const int kBlockSizes[] = {64, 128, 256, 512, 1024};
 const int kNumBlockSizes = 5;
 const long long kStageNodes = 1 << 20;
+const size_t kStoreBatch = 8;  // replicas from which the store policy is that of batches
 
 struct Totals {
     long long nodes = 0;
@@ -1044,7 +1045,13 @@ int lb_init(const lbmd_config* cfg, const lbmd_buffers* bufs, void* hip_stream, 
     // A lattice step of one box, stored normally / streamed, us: 174 MB 30.5 / 38.4, 224 MB
     // 38.0 / 50.9, 261 MB 43.3 / 54.8, 299 MB 56.8 / 59.7 (FP32); 319 MB 63.2 / 67.2 (FP16) and
     // 60.8 / 64.5 (FP64); 398 MB 86.0 / 84.4 (FP16) and 83.1 / 81.2 (FP64); 598 MB 117.6 / 114.6.
-    c.lat_nt = 2.0 * (double)c.pop_elems * (double)store_size(c.storage) > 340e6;
+    // Up to 7 replicas go like one box: 7 of 100x50x50 (FP32, 266 MB) 49.9 / 51.3, with a thermal
+    // source 55.6 / 55.6; 3 of 128x96x96 (BF16, 269 MB) 53.7 / 62.0.  Larger batches, with tiles in
+    // hardware order over many small boxes, only while they fit the cache: 28 of 48^3 (FP16, 235 MB)
+    // 37.7 / 46.7, 32 (269 MB) 54.4 / 49.6; 17 in FP32 (286 MB) 55.8 / 54.2; 8 of 100x50x50 with a
+    // thermal source (FP32, 304 MB) 65.0 / 61.5.
+    c.lat_nt = 2.0 * (double)c.pop_elems * (double)store_size(c.storage) > 
+               (c.reps.size() < kStoreBatch ? 340e6 : 256e6);
 
     if ((rc = check(hipStreamCreateWithFlags(&c.side, hipStreamNonBlocking), "side stream"))) return bail(rc);
     if ((rc = check(hipStreamCreateWithFlags(&c.cap, hipStreamNonBlocking), "capture stream"))) return bail(rc);
