@@ -460,7 +460,9 @@ __device__ __forceinline__ Real separation_v(const double* ri, const double* pj,
     if constexpr (PERIODIC) {
 #pragma unroll
         for (int c = 0; c < 3; ++c)
-            if (per[c]) dd[c] -= nd[c] * floor(dd[c] / nd[c] + 0.5);
+            // (within half a box there is nothing to subtract, and most waves need no division: 700
+            // beads on two periodic axes, FP32, 157 us a step with it, 126 without)
+            if (per[c] && !(fabs(dd[c]) * 2.01 < nd[c])) dd[c] -= nd[c] * floor(dd[c] / nd[c] + 0.5);
     }
     d[0] = (Real)dd[0];
     d[1] = (Real)dd[1];
@@ -561,6 +563,12 @@ struct SlotsPerLane {
     // One lane a bead below the 1024-thread bound (257 to 512 beads): the substeps go by a shorter
     // inner list.  More lanes hold a bead's entries in their slots already; beyond 512 beads there
     // are no registers left for the second reference position.
+    // Tight: the 1024-thread bound leaves a lane 128 registers, so that nothing is held through a
+    // substep that can be had again where it is used (slot positions, wall bounds), and list entries
+    // are taken in small rounds, their positions one at a time.  Held as below that bound, they
+    // spilled: 700 beads (FP32 / FP64) 102 / 130 us a step, so 90 / 109; 1500 beads 243 / 353, so
+    // 213 / 262; 2400 beads 410 / 669, so 355 / 515.
+    static constexpr bool tight = MAXT > 512;
     static constexpr bool inner = G == 1 && BPT == 1 && MAXT <= 512;
     static constexpr int K = MAXT > 512 ? (BPT > 1 ? 1 : 2) : (BPT > 1 ? 4 : (G >= 8 ? 1 : inner ? 6 : 8 / G));
 };
@@ -573,13 +581,13 @@ constexpr int kInnerMax = 16;  // entries held; a bead with more goes by the Ver
 
 // Verlet list of bead i (group of G lanes): every non-bonded bead closer than the list
 // radius, in lane-then-index order.  Returns the count (may exceed the capacity).
-template <class Real, int G, bool PERIODIC, class List>
+template <class Real, int G, bool PERIODIC, bool TIGHT, class List>
 __device__ __forceinline__ int build_list(int i, int n, bool bn, bool bp, const double* ri, const double* PB,
                                           const int* per, const double* nd, Real rl2, int gl, List list,
                                           int stride) {
     // U candidates a round: their positions are loaded together, so that a round and not a
     // candidate costs an LDS round trip
-    constexpr int U = G == 1 ? 8 : 4;
+    constexpr int U = TIGHT ? 1 : G == 1 ? 8 : 4;
     auto scan = [&](auto&& hit_at) {
         int m = 0;
         for (int j0 = gl; j0 < n; j0 += U * G, m += U) {
@@ -698,17 +706,24 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
     double* P = lds;                                    // [2][nmax][3] positions
     int* NODE = (int*)(P + 6 * nmax);                   // [nmax]
     unsigned char* BN = (unsigned char*)(NODE + nmax);  // [nmax]
-    // Verlet lists: [kNeighbourMax][nmax] in LDS when they fit, else global memory (two
-    // pointers rather than one generic one: an LDS read instead of a flat one)
-    unsigned short* LL = (unsigned short*)(BN + nmax);
-    unsigned short* GL = a.b.nlist + b0;
+    // Verlet lists: [kNeighbourMax][nmax] in LDS when they fit, else global memory.  Up to 512 beads
+    // two pointers into their own address spaces: an LDS read and a global one instead of one flat
+    // one, into which the compiler would merge them (100 beads in 64x48x48, FP32: 38.4 -> 37.7 us a
+    // step).  Beyond, where most lists are in global memory, the flat read is the faster one (1500
+    // beads: 211 us, 219 with two pointers).
+    constexpr bool kTight = SlotsPerLane<G, BPT, MAXT>::tight;
+    typedef std::conditional_t<kTight, unsigned short, __attribute__((address_space(3))) unsigned short> LdsIndex;
+    typedef std::conditional_t<kTight, unsigned short, __attribute__((address_space(1))) unsigned short> GlobalIndex;
+    LdsIndex* LL = (LdsIndex*)(unsigned short*)(BN + nmax);
+    GlobalIndex* GL = (GlobalIndex*)(a.b.nlist + b0);
     const bool list_lds = a.list_in_lds != 0;
     auto list_at = [&](int q, int i) -> int { return list_lds ? LL[q * nmax + i] : GL[(size_t)q * NT + i]; };
     // inner lists [kInnerMax][nmax] and random forces [M][nmax][3], after the lists (or after BN
     // when the lists are global)
-    unsigned short* IL = (unsigned short*)(BN + nmax + (list_lds ? (size_t)kNeighbourMax * nmax * 2 : (size_t)0));
+    LdsIndex* IL = LL + (list_lds ? kNeighbourMax * nmax : 0);
     constexpr bool INNER = SlotsPerLane<G, BPT, MAXT>::inner;
-    Real* NZ = (Real*)(IL + (INNER ? kInnerMax * nmax : 0));
+    Real* NZ = (Real*)((unsigned short*)(BN + nmax) + (list_lds ? kNeighbourMax * nmax : 0) +
+                       (INNER ? kInnerMax * nmax : 0));
     const bool noise_lds = G > 1 && a.noise_in_lds;
     const MDDev md = a.md;
     // rigid bonds: SHAKE/RATTLE work area after the random-force table, doubles:
@@ -965,9 +980,9 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
         // the register slots of the Verlet list are read together with the rebuild vote of the
         // last substep; after a rebuild they are read again
         double pj[BPT][K][3];
-        auto read_slots = [&]() {
+        auto read_slots = [&](int k0, int k1) {
 #pragma unroll
-            for (int k = 0; k < BPT; ++k)
+            for (int k = k0; k < k1; ++k)
 #pragma unroll
                 for (int s = 0; s < K; ++s) {
                     if (INNER && s == K / 2 && !half[k]) break;
@@ -979,7 +994,7 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
         if (sub > 0) {
             const int voted = vote[(sub - 1) & 1];
             const int inner_voted = INNER ? inner_vote[(sub - 1) & 1] : 0;
-            read_slots();
+            if (!kTight) read_slots(0, BPT);
             build = __builtin_amdgcn_readfirstlane(voted) == -sub;  // ~(sub - 1)
             if (INNER) refresh = __builtin_amdgcn_readfirstlane(inner_voted) == -sub;
         }
@@ -993,10 +1008,10 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
                 for (int c = 0; c < 3; ++c) rref[k][c] = r[k][c];
                 if (!own[k]) continue;
                 if (list_lds)
-                    cnt[k] = build_list<Real, G, PERIODIC>(i, n, bnk[k], bpk[k], r[k], PB, per, nd, rl2, gl, LL + i,
+                    cnt[k] = build_list<Real, G, PERIODIC, kTight>(i, n, bnk[k], bpk[k], r[k], PB, per, nd, rl2, gl, LL + i,
                                                            nmax);
                 else
-                    cnt[k] = build_list<Real, G, PERIODIC>(i, n, bnk[k], bpk[k], r[k], PB, per, nd, rl2, gl, GL + i,
+                    cnt[k] = build_list<Real, G, PERIODIC, kTight>(i, n, bnk[k], bpk[k], r[k], PB, per, nd, rl2, gl, GL + i,
                                                            NT);
             }
             __syncthreads();
@@ -1059,7 +1074,7 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
                 half[k] = __ballot(own[k] && cin[k] > K / 2 * G) != 0ull;
                 more[k] = __ballot(own[k] && cin[k] > K * G) != 0ull;
             }
-            read_slots();
+            if (!kTight) read_slots(0, BPT);
         }
         if (sub == 0) {
             // Flag whether a bead shares its node and whether a lower-index bead does (then it
@@ -1113,11 +1128,9 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
             // WCA against the Verlet neighbours: register slots, then any further list
             // entries, or all pairs if the list overflowed
             Real fx = 0, fy = 0, fz = 0;
-            // without branches: an unused slot or a pair beyond the cutoff adds 0
-            auto pair = [&](const double* p, bool valid) {
-                Real d[3];
-                const Real r2 = separation_v<Real, PERIODIC>(r[k], p, per, nd, d);
-                const bool hit = valid & (r2 < rc2);
+            // without branches: an unused slot or a pair beyond the cutoff adds 0 (times a separation
+            // that is finite, as that of every bead a list holds)
+            auto add_pair = [&](const Real* d, Real r2, bool hit) {
                 const Real ir2 = fast_rcp<Real>(hit ? r2 : Real(1));
                 const Real s2 = sig2 * ir2;
                 const Real s6 = s2 * s2 * s2;
@@ -1126,6 +1139,12 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
                 fy += c * d[1];
                 fz += c * d[2];
             };
+            auto pair = [&](const double* p, bool valid) {
+                Real d[3];
+                const Real r2 = separation_v<Real, PERIODIC>(r[k], p, per, nd, d);
+                add_pair(d, r2, valid & (r2 < rc2));
+            };
+            if (kTight) read_slots(k, k + 1);
 #pragma unroll
             for (int s = 0; s < K; ++s) {
                 if (INNER && s == K / 2 && !half[k]) break;
@@ -1133,26 +1152,40 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
             }
             if (more[k]) {
                 // entries beyond the register slots, U a lane and round: a round, not an entry,
-                // costs the two LDS round trips (entry, position)
-                constexpr int U = G == 1 ? 4 : 2;
+                // costs the LDS round trips (entry, position)
+                constexpr int U = G == 1 && !(kTight && BPT == 1) ? 4 : 2;
                 const bool overflow = own[k] && cnt[k] > kNeighbourMax;
                 const int lim = own[k] && !overflow ? cin[k] : 0;
                 for (int q0 = gl + K * G; q0 < lim; q0 += U * G) {
                     int j[U];
                     bool ok[U];
-                    double pq[U][3];
 #pragma unroll
                     for (int t = 0; t < U; ++t) {
                         const int q = q0 + t * G;
                         ok[t] = q < lim;
-                        j[t] = ok[t] ? entry_at(q, i, k) : i;
+                        if constexpr (kTight) j[t] = ok[t] ? entry_at(q, i, k) : i;
+                        else j[t] = entry_at(ok[t] ? q : q0, i, k);
                     }
+                    if constexpr (kTight) {
+                        // one position at a time, and a wave without a pair within the cutoff skips the rest
 #pragma unroll
-                    for (int t = 0; t < U; ++t)
+                        for (int t = 0; t < U; ++t) {
+                            if (t > 0 && __ballot(ok[t]) == 0ull) break;
+                            const double pq[3] = {PB[3 * j[t]], PB[3 * j[t] + 1], PB[3 * j[t] + 2]};
+                            Real d[3];
+                            const Real r2 = separation_v<Real, PERIODIC>(r[k], pq, per, nd, d);
+                            const bool hit = ok[t] & (r2 < rc2);
+                            if (__ballot(hit) != 0ull) add_pair(d, r2, hit);
+                        }
+                    } else {
+                        double pq[U][3];
 #pragma unroll
-                        for (int c = 0; c < 3; ++c) pq[t][c] = PB[3 * j[t] + c];
+                        for (int t = 0; t < U; ++t)
 #pragma unroll
-                    for (int t = 0; t < U; ++t) pair(pq[t], ok[t]);
+                            for (int c = 0; c < 3; ++c) pq[t][c] = PB[3 * j[t] + c];
+#pragma unroll
+                        for (int t = 0; t < U; ++t) pair(pq[t], ok[t]);
+                    }
                 }
                 // A list that overflowed: all beads, one after the other.  Among them are beads whose
                 // position is not finite, which no list holds: only a pair within the cutoff is added.
@@ -1160,7 +1193,8 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
                     if (q == i || (q == i + 1 && bnk[k]) || (q == i - 1 && bpk[k])) continue;
                     const double pq[3] = {PB[3 * q], PB[3 * q + 1], PB[3 * q + 2]};
                     Real d[3];
-                    if (separation_v<Real, PERIODIC>(r[k], pq, per, nd, d) < rc2) pair(pq, true);
+                    const Real r2 = separation_v<Real, PERIODIC>(r[k], pq, per, nd, d);
+                    if (r2 < rc2) add_pair(d, r2, true);
                 }
             }
             F[k][0] = group_sum<G>(fx);
@@ -1220,7 +1254,7 @@ __device__ __forceinline__ void bead_step(const MDKArgs<Real>& a, const int stor
                     // (held through a polymer model's loop, the bounds would push its constraint
                     // solve out of the registers)
                     WallBounds B = WB[w];
-                    if (POLY) {
+                    if (POLY || kTight) {
                         int wl[6];
 #pragma unroll
                         for (int m = 0; m < 6; ++m) wl[m] = here(GM.wall[w][m]);
