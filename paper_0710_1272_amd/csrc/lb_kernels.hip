@@ -35,7 +35,6 @@ __global__ __launch_bounds__(BLOCK) void k_stream_collide(const Replica* __restr
         return;
     }
     // one wave per row segment: y, z and the face decisions are wave-uniform
-    Rl f[Q];
     constexpr int W = BLOCK / 64;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const RowUnit U = row_unit(R, (tile - prefix[r]) * W + wave);
@@ -51,13 +50,18 @@ __global__ __launch_bounds__(BLOCK) void k_stream_collide(const Replica* __restr
         if (k >= R.n_walls) break;
         zone = zone || (U.x0 <= R.wall[k][1] + 1 && U.x0 + 63 >= R.wall[k][0] - 1);
     }
+    typename C::T g[Q];
     if (!solid) {
-        if (zone) gather_row<S, true>(R, src, idx, x, y, z, f);
-        else gather_row<S, false>(R, src, idx, x, y, z, f);
-        relax_node<S, TH>(R, f, idx, st);
-    } else {
-        rest_slots<S>(R, f);
+        if (zone) gather_row<S, true>(R, src, idx, x, y, z, g);
+        else gather_row<S, false>(R, src, idx, x, y, z, g);
     }
+    Rl f[Q];
+    for_pops([&](auto P) {
+        constexpr int p = decltype(P)::value;
+        f[p] = C::load_raw(g[p]);
+    });
+    if (solid) rest_slots<S>(R, f);
+    else relax_node<S, TH>(R, f, idx, st);
     store_node<S, NT>(R, f, dst, idx);
 }
 
