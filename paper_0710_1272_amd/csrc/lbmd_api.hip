@@ -174,7 +174,7 @@ WorkLayout work_layout(int n_reps, int max_V, long long max_stage_nodes, int chu
     off += align256(sizeof(RunState));
     L.partial_blocks = 32768;  // capacity: one block of partial sums per 4096 nodes up to 2^27 nodes
     L.partials = off;
-    off += align256(sizeof(double) * (4 * (size_t)L.partial_blocks + 4));
+    off += align256(sizeof(double) * 4 * (size_t)L.partial_blocks);
     const long long stage_nodes = std::min<long long>(max_V, max_stage_nodes);
     L.stage_doubles = (size_t)(19 * stage_nodes);
     L.stage = off;
@@ -1223,10 +1223,6 @@ int lb_md_lanes(const lbmd_ctx* ctx) {
     if (c.ntot_beads == 0) return 0;
     return c.md_lanes > 0 ? c.md_lanes : md_default_lanes(c.max_beads);
 }
-
-}  // extern "C"
-
-extern "C" {
 
 int lb_moments(lbmd_ctx* ctx, int replica, unsigned what, void* host_out, size_t bytes) {
     if (!ctx) return fail(LB_EINVAL, "ctx is NULL");

@@ -234,60 +234,14 @@ __host__ __device__ __forceinline__ int mirror_combo(bool fx, bool fy, bool fz) 
     return fx ? (fy ? (fz ? mxyz : mxy) : (fz ? mxz : mx)) : (fy ? (fz ? myz : my) : (fz ? mz : P));
 }
 
-// Face resolution of the pull source of population P at node (x,y,z): s = x - c_P; a periodic
-// axis wraps, a free-slip axis keeps x_a and reflects component a.  No solidity test.  Returns
-// the node index within the replica, its coordinates in sc[3] and the population stored there
-// in *q.
-template <int P>
-__host__ __device__ __forceinline__ int pull_resolve(const Replica& R, int x, int y, int z, int* sc, int* q) {
-    constexpr int cx = cx_of(P), cy = cy_of(P), cz = cz_of(P);
-    int sx = x - cx, sy = y - cy, sz = z - cz;
-    bool fx = false, fy = false, fz = false;
-    if constexpr (cx != 0) {
-        if (sx < 0 || sx >= R.nx) {
-            if (R.fs[0]) { sx = x; fx = true; }
-            else sx += sx < 0 ? R.nx : -R.nx;
-        }
-    }
-    if constexpr (cy != 0) {
-        if (sy < 0 || sy >= R.ny) {
-            if (R.fs[1]) { sy = y; fy = true; }
-            else sy += sy < 0 ? R.ny : -R.ny;
-        }
-    }
-    if constexpr (cz != 0) {
-        if (sz < 0 || sz >= R.nz) {
-            if (R.fs[2]) { sz = z; fz = true; }
-            else sz += sz < 0 ? R.nz : -R.nz;
-        }
-    }
-    *q = mirror_combo<P>(fx, fy, fz);
-    sc[0] = sx;
-    sc[1] = sy;
-    sc[2] = sz;
-    return sx + R.nx * (sy + R.ny * sz);
-}
-
-// Pull resolver for a fluid node (x,y,z) and population P: where the value that
-// arrives in slot (x,P) was stored after the previous collision.  The face-resolved
-// source, or, when that source is solid, slot (x, opp(P)): the population bounced back.
-// Returns the node index within the replica; *q receives the population.
-template <int P>
-__host__ __device__ __forceinline__ int pull_source(const Replica& R, int x, int y, int z, int* q) {
-    int sc[3];
-    const int s = pull_resolve<P>(R, x, y, z, sc, q);
-    if (is_solid(R, sc[0], sc[1], sc[2])) {
-        *q = opp_of(P);
-        return x + R.nx * (y + R.ny * z);
-    }
-    return s;
-}
-
-// The pull sources of all 19 populations of one fluid node, resolved without a branch per
-// population.  pull_source's tests compile to control flow around every population, which puts
-// a wait between one population's load and the next: a gather through it is 19 dependent round
-// trips (12 us of the bead kernel's 37 us at 128x64x64).  Here each axis resolves its two
-// neighbour coordinates once (wrapped, or kept and reflected), each wall folds into the
+// The pull sources of all 19 populations of one fluid node: where the value that arrives in slot
+// (x, P) was stored after the previous collision.  That is population P at s = x - c_P; on an axis
+// where s lies beyond the box it is the periodic image, or at a free-slip face the node's own
+// coordinate with that component of the population reflected; and when that source is solid, slot
+// (x, opp(P)), the population bounced back.  Resolved without a branch per population: tests around
+// every population put a wait between one population's load and the next, so that a gather was 19
+// dependent round trips (12 us of the bead kernel's 37 us at 128x64x64).  Here each axis resolves its
+// two neighbour coordinates once (wrapped, or kept and reflected), each wall folds into the
 // solidity bits of the 27 resolved neighbours, and a population's element is selects over
 // those, so that the caller can issue all 19 loads before it uses the first.
 struct PullMap {
@@ -348,8 +302,8 @@ __host__ __device__ __forceinline__ long long pull_element(const Replica& R, con
     return (long long)q * R.S + (solid ? m.node : s);
 }
 
-// Face resolution of the push target of population QP leaving node (sx,sy,sz), the inverse of
-// pull_resolve: t = s + c_QP, a periodic axis wraps, a free-slip axis keeps s_a and reflects
+// Face resolution of the push target of population QP leaving node (sx,sy,sz), the inverse of the
+// pull source's: t = s + c_QP, a periodic axis wraps, a free-slip axis keeps s_a and reflects
 // component a.  No solidity test.  Returns the node index, its coordinates in tc[3] and the
 // population that arrives there in *p.
 template <int QP>
@@ -382,7 +336,7 @@ __host__ __device__ __forceinline__ int push_resolve(const Replica& R, int sx, i
     return tx + R.nx * (ty + R.ny * tz);
 }
 
-// Push resolver (inverse of pull_source): where population Q leaving fluid node s
+// Push resolver (inverse of the pull): where population Q leaving fluid node s
 // ends up, bounced back into (s, opp(Q)) when the face-resolved target is solid.  Used to
 // build a post-collision buffer whose pull gives wanted populations.
 template <int QP>

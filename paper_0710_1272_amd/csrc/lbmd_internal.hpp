@@ -110,10 +110,17 @@ struct WorkLayout {
     int n_prefix_tables;
 };
 WorkLayout work_layout(int n_reps, int max_V, long long max_stage_nodes, int chunks);
-// Largest box of the one-launch step (k_step_one).  Its sweep runs at two waves a SIMD, which a bead
-// step of 33-40 us hides up to here: 128x128x80 (these 1.3e6 nodes) takes 38.7 us a step for 100 beads
-// in FP16 and 41.3 in FP32, against 44.9 and 61.8 as separate launches; 128x128x120 in FP16 with 20
-// beads 52.0 against 44.1.
+// Largest box of the one-launch step (k_step_one).  Its sweep runs at two waves a SIMD, which the bead
+// step hides up to here, or the launches it saves pay for.  A step of 128x128x80 (these 1.3e6 nodes),
+// us, in one launch / in separate ones:
+//              12 beads, M = 5    100, M = 5   200, M = 20   100 rigid, M = 5
+//   FP64           89 / 95          89 / 97      90 / 98        90 / 98
+//   FP32           39 / 47          39 / 48      53 / 55        66 / 69
+//   FP16, BF16     34 / 34          34 / 34      49 / 52        65 / 68
+// and of 128x64x64 32 / 42 (FP64), 20 / 30 (FP32), 17 / 25 (FP16) for 12 beads; M = 1 as M = 5.  The
+// one launch loses with 16-bit storage near the limit when the bead step is short but for M: 12 beads,
+// M = 20 36 / 33; and by 1-2 % in FP64 with a rigid chain below it.  Beyond, 128x128x120 in FP16 with 20
+// beads takes 52 / 44.
 constexpr int kStepOneNodes = 5 << 18;
 // chunks with marks of a configuration: those of a box that may take the one-launch step, else 0
 int mark_chunks(const lbmd_config* cfg);
