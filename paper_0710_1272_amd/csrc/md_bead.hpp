@@ -1621,8 +1621,8 @@ __global__ __launch_bounds__(MAXT) void k_md(MDKArgs<Real> a, int storage) {
 // there; the others sweep every other node.  Nobody waits for anybody, so that the launch boundary
 // is the only ordering.  Bound by the bead step, a chain of latencies in one workgroup: as launches
 // of their own it, the sweep and the spread also paid for a dependency between two queues and for
-// the launch that followed (128x64x64, 100 beads, FP32: 45.3 us a step, here 40.0; rigid 74.4 and
-// 66.5; 12 beads in 48x24x24: 36.8 and 30.3).  The sweep runs with the bead step's registers, two
+// the launch that followed (128x64x64, 100 beads, FP32: 42.0 us a step, here 35.8; rigid 70.5 and
+// 67.3; 12 beads in 64x32x32: 31.4 and 26.9).  The sweep runs with the bead step's registers, two
 // waves a SIMD, which it hides in a box this small.
 template <int S, class Real, int G, bool POLY>
 __global__ __launch_bounds__(512) void k_step_one(MDKArgs<Real> a, int bead_threads, int tiles) {

@@ -450,8 +450,8 @@ hipError_t launch_md(const Context& c, const void* cur, int mode, hipStream_t s,
 
 // One lane a bead (more than 256 beads by default) stays with separate launches: the bead step then
 // needs every register, and beside the sweep's code it spills (400 beads in 96x48x48, FP32: 90.9 us a
-// step in one launch, 83.8 apart; 200 beads, two lanes each: 54.6 and 59.2; 100 beads in 128x64x64:
-// 40.0 and 45.3, rigid 66.5 and 74.4; 12 beads in 48x24x24: 30.3 and 36.8).
+// step in one launch, 83.8 apart; in 128x64x64 200 beads, two lanes each: 51.6 and 53.4; 100 beads
+// 35.8 and 42.0, rigid 67.3 and 70.5; 12 beads in 64x32x32: 26.9 and 31.4).
 bool step_one_fits(const Context& c) {
     if (!c.one_launch || !c.marks[0].stamp || c.obs_every > 0) return false;
     return step_one_lanes(c.md_lanes > 0 ? c.md_lanes : md_default_lanes(c.max_beads), c.max_beads);
