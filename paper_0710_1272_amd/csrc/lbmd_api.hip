@@ -758,7 +758,10 @@ int autotune_route(Context& c, int given_lanes) {
     const size_t bead_bytes = bead_layout(c.ntot_beads, (int)c.reps.size(), real, 0, false).total;
     const size_t pop_bytes = align256((size_t)c.pop_elems * store_size(c.storage));
     char* save = nullptr;
-    HIP_TRY(hipMalloc((void**)&save, pop_bytes + bead_bytes + sizeof(RunState)));
+    if (hipMalloc((void**)&save, pop_bytes + bead_bytes + sizeof(RunState)) != hipSuccess) {
+        (void)hipGetLastError();  // no room to put the state back from: the choice by size stays
+        return LB_OK;
+    }
     hipEvent_t e0 = nullptr, e1 = nullptr;
     hipGraphExec_t g = nullptr;
     auto copy = [&](void* dst, const void* src, size_t n) {
